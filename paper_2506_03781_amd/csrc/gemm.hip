@@ -10,16 +10,21 @@
 // ("NT"), so one kernel template serves them.  The block's backpropagation
 // also takes operands stored K-slow (A as [K x M], B as [K x N]): the weight
 // gradient dY^T X and the input gradient dY W read the activations and the
-// weights as they are stored, with no transposed copies (ping-pong kernel
-// only; the copies take whole k-rows and the MFMA fragments come from LDS
-// transpose reads).
+// weights as they are stored, with no transposed copies (four-wavefront and
+// ping-pong kernels; the copies take whole k-rows and the MFMA fragments come
+// from LDS transpose reads).
 //
-// Kernels (all bf16 MFMA v_mfma_f32_32x32x16_bf16, fp32 accumulation):
-//   gemm_pp_kernel    the main one, for K % 32 == 0 on 256 x 256 and 256 x 128
-//                     tiles: eight wavefronts in two groups that alternate
-//                     ("ping-pong") between an MFMA phase and a memory phase
-//                     (LDS fragment reads, global_load_lds copies into a ring
-//                     of 32- or 64-deep stages, exact vmcnt waits, barriers);
+// Kernels (all bf16 MFMA with fp32 accumulation, v_mfma_f32_32x32x16_bf16
+// unless stated; the same sums in the same order either way):
+//   gemm_w4_kernel    the main one, for K % 64 == 0 on 256 x 256 tiles: four
+//                     wavefronts of 128 x 128 (v_mfma_f32_16x16x32_bf16), two
+//                     64-deep stages, the instruction order fixed by hand;
+//   gemm_pp_kernel    K % 32 == 0 on 256 x 128 tiles, and on 256 x 256 tiles
+//                     where K % 64 == 32: eight wavefronts in two groups that
+//                     alternate ("ping-pong") between an MFMA phase and a
+//                     memory phase (LDS fragment reads, global_load_lds copies
+//                     into a ring of 32- or 64-deep stages, exact vmcnt waits,
+//                     barriers);
 //   gemm_pipe_kernel  four wavefronts, the same direct-to-LDS stage ring, for
 //                     128 x 128 tiles (shapes too small to fill the GPU with
 //                     256-row tiles);
@@ -33,6 +38,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "uq_launch.h"
 
@@ -40,6 +46,7 @@ namespace uq {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct GemmArgs {
   const uint16_t* A;
@@ -83,6 +90,12 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
 }
 
+// Column at which an epilogue strip keeps element (row, col): 16-column halves
+// swap on rows with bit 2 set, so that the accumulator writes of both MFMA
+// layouts (rows 4 apart in lanes 16 or 32 apart) fall in distinct banks;
+// aligned runs of up to 16 columns stay contiguous.
+__device__ __forceinline__ int strip_col(int row, int col) { return col ^ (((row >> 2) & 1) << 4); }
+
 // A 32-row strip of one head (128 columns, fp32 in LDS, row stride 128) to
 // the head-major bf16 output: element (row_base + r, h * 128 + j) goes to
 // out[(slot(h) * M + row_base + r) * 128 + j], with the pairs (j, j + 64)
@@ -103,8 +116,8 @@ __device__ __forceinline__ void heads_strip(const GemmArgs& p, const float* stri
     const int r = (lane >> 4) + 4 * k;
     const int64_t m = row_base + r;
     if (m >= p.M) break;
-    const float4 a = *reinterpret_cast<const float4*>(&strip[r * 128 + i0]);
-    const float4 b = *reinterpret_cast<const float4*>(&strip[r * 128 + 64 + i0]);
+    const float4 a = *reinterpret_cast<const float4*>(&strip[r * 128 + strip_col(r, i0)]);
+    const float4 b = *reinterpret_cast<const float4*>(&strip[r * 128 + 64 + strip_col(r, i0)]);
     float x1[4] = {p.scale * a.x, p.scale * a.y, p.scale * a.z, p.scale * a.w};
     float x2[4] = {p.scale * b.x, p.scale * b.y, p.scale * b.z, p.scale * b.w};
     float y1[4], y2[4];
@@ -211,8 +224,9 @@ __device__ __forceinline__ void ste_strip(const GemmArgs& p, const float* strip,
       const float dl = dlv[j];
       if (act[j]) {
         float G[8], w[8];
-        const float4 g0 = *reinterpret_cast<const float4*>(strip + lrow * 128 + c8);
-        const float4 g1 = *reinterpret_cast<const float4*>(strip + lrow * 128 + c8 + 4);
+        const float* sg = strip + lrow * 128 + strip_col(lrow, c8);
+        const float4 g0 = *reinterpret_cast<const float4*>(sg);
+        const float4 g1 = *reinterpret_cast<const float4*>(sg + 4);
         G[0] = p.scale * g0.x; G[1] = p.scale * g0.y; G[2] = p.scale * g0.z; G[3] = p.scale * g0.w;
         G[4] = p.scale * g1.x; G[5] = p.scale * g1.y; G[6] = p.scale * g1.z; G[7] = p.scale * g1.w;
         if (q.w_bf16) {
@@ -272,47 +286,69 @@ __device__ __forceinline__ void ste_strip(const GemmArgs& p, const float* strip,
   }
 }
 
+// Write rows 32 i .. 32 i + 31 of a wavefront's accumulator tile to its strip.
+// 32x32 MFMA blocks: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4
+// and column l%32.
+template <int WN, int FM, int FN>
+__device__ __forceinline__ void write_strip(const f32x16 (&acc)[FM][FN], int i, int lane, float* strip) {
+  const int lr = lane & 31, lh = lane >> 5;
+#pragma unroll
+  for (int j = 0; j < FN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
+      strip[row * WN + strip_col(row, j * 32 + lr)] = acc[i][j][r];
+    }
+}
+
+// 16x16 MFMA blocks: register r of lane l holds row 4*(l/16) + r and column l%16.
+template <int WN, int FM, int FN>
+__device__ __forceinline__ void write_strip(const f32x4 (&acc)[FM][FN], int i, int lane, float* strip) {
+  const int lc = lane & 15, lq = lane >> 4;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * h + 4 * lq + r;
+        strip[row * WN + strip_col(row, j * 16 + lc)] = acc[2 * i + h][j][r];
+      }
+}
+
 // Store an accumulator tile with the requested epilogue, staged through LDS
-// one 32-row strip at a time.  Accumulator register r of lane l of a 32x32
-// MFMA block holds row 8*(r/4) + 4*(l/32) + r%4 and column l%32; each wave
-// writes its strip (32 x WN fp32) to its own LDS region, then reads it back
-// as rows of float4 so that the target is loaded and the output stored as
-// contiguous 16-byte / 8-byte vectors.  `scratch` must hold 4 * 32 * WN
-// floats and may alias the operand stages (all waves are past their last
-// operand read when this is called).
-template <int BM, int BN, int EPI, int WM = BM / 2, int WN = BN / 2, int NW = 4, int FM = WM / 32,
-          int FN = WN / 32>
-__device__ __forceinline__ void epilogue(const GemmArgs& p, f32x16 (&acc)[FM][FN], int64_t m0, int64_t n0,
-                                         int wm, int wn, int lane, int wave, int tid, float* scratch) {
+// one 32-row strip at a time: each wave writes its strip (32 x WN fp32) to its
+// own LDS region, then reads it back as rows of float4 so that the target is
+// loaded and the output stored as contiguous 16-byte / 8-byte vectors.
+// `scratch` must hold NW * (32 * WN + 1) floats and may alias the operand stages
+// (all waves are past their last operand read when this is called).
+template <int BM, int BN, int EPI, int WM = BM / 2, int WN = BN / 2, int NW = 4, typename Acc>
+__device__ __forceinline__ void epilogue(const GemmArgs& p, const Acc& acc, int64_t m0, int64_t n0, int wm, int wn,
+                                         int lane, int wave, int tid, float* scratch) {
   constexpr int Q = WN / 4;            // float4 per strip row
   constexpr int ITER = 32 * Q / 64;    // float4 per lane per strip
-  const int lr = lane & 31, lh = lane >> 5;
   float* strip = scratch + wave * 32 * WN;
   const bool full = (m0 + BM <= p.M) && (n0 + BN <= p.N);
   const float* __restrict__ Yt = p.Yt;
   float lsum = 0.0f;
 #pragma unroll
-  for (int i = 0; i < FM; ++i) {
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        strip[(8 * (r >> 2) + 4 * lh + (r & 3)) * WN + j * 32 + lr] = acc[i][j][r];
+  for (int i = 0; i < WM / 32; ++i) {
+    write_strip<WN>(acc, i, lane, strip);
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the strip is written (own wave only)
     __builtin_amdgcn_wave_barrier();
     const int64_t row_base = m0 + wm * WM + i * 32;
     const int64_t col_base = n0 + wn * WN;
     if constexpr (EPI == EPI_SWIGLU) {
-      static_assert(WN == 64, "the SiLU product needs 64-column wave tiles (G and U halves)");
-      // strip columns 0..31: G, 32..63: U of rows I0 .. I0 + 31 of W
-      const int64_t I = p.swiglu.I, i0 = n0 / 2 + wn * 32;
+      static_assert(WN % 64 == 0, "the SiLU product needs 64-column blocks (G and U halves)");
+      // strip columns 64 b .. 64 b + 31: G, 64 b + 32 .. 64 b + 63: U of the same 32 rows of W
+      const int64_t I = p.swiglu.I;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int item = lane + 64 * k, rr = item >> 3, cq = (item & 7) * 4;
-        const int64_t m = row_base + rr;
+      for (int k = 0; k < 4 * (WN / 64); ++k) {
+        const int item = lane + 64 * (k & 3), rr = item >> 3, cq = (item & 7) * 4, cb = 64 * (k >> 2);
+        const int64_t m = row_base + rr, i0 = n0 / 2 + wn * (WN / 2) + 32 * (k >> 2);
         if (m >= p.M || i0 + cq >= I) continue;
-        const float4 g4 = *reinterpret_cast<const float4*>(&strip[rr * 64 + cq]);
-        const float4 u4 = *reinterpret_cast<const float4*>(&strip[rr * 64 + 32 + cq]);
+        const float4 g4 = *reinterpret_cast<const float4*>(&strip[rr * WN + cb + strip_col(rr, cq)]);
+        const float4 u4 = *reinterpret_cast<const float4*>(&strip[rr * WN + cb + 32 + strip_col(rr, cq)]);
         const uint32_t g01 = pack_bf16x2(p.scale * g4.x, p.scale * g4.y), g23 = pack_bf16x2(p.scale * g4.z, p.scale * g4.w);
         const uint32_t u01 = pack_bf16x2(p.scale * u4.x, p.scale * u4.y), u23 = pack_bf16x2(p.scale * u4.z, p.scale * u4.w);
         const float gf[4] = {__uint_as_float(g01 << 16), __uint_as_float(g01 & 0xFFFF0000u),
@@ -349,7 +385,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& p, f32x16 (&acc)[FM][FN
         const int item = lane + 64 * k, rr = item / (WN / 4), cq = (item % (WN / 4)) * 4;
         const int64_t m = row_base + rr, n = col_base + cq;
         if (m >= p.M || n >= p.N) continue;
-        const float4 v = *reinterpret_cast<const float4*>(&strip[rr * WN + cq]);
+        const float4 v = *reinterpret_cast<const float4*>(&strip[rr * WN + strip_col(rr, cq)]);
         const uint32_t h01 = pack_bf16x2(p.scale * v.x, p.scale * v.y), h23 = pack_bf16x2(p.scale * v.z, p.scale * v.w);
         const uint32_t hw[2] = {h01, h23}, gw[2] = {gq[k].x, gq[k].y}, uw[2] = {uq4[k].x, uq4[k].y};
         float dg[4], du[4];
@@ -410,7 +446,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& p, f32x16 (&acc)[FM][FN
     }
     auto put = [&](int it) {
       const int idx = lane + it * 64, rr = idx / Q, cc = (idx % Q) * 4;
-      const float4 v = *reinterpret_cast<const float4*>(&strip[rr * WN + cc]);
+      const float4 v = *reinterpret_cast<const float4*>(&strip[rr * WN + strip_col(rr, cc)]);
       const int64_t o = base + rr * ldn + cc;
       if constexpr (EPI == EPI_TARGET) {
         *reinterpret_cast<float4*>(static_cast<float*>(p.out) + o) = v;
@@ -459,7 +495,9 @@ __device__ __forceinline__ void epilogue(const GemmArgs& p, f32x16 (&acc)[FM][FN
     __builtin_amdgcn_wave_barrier();
   }
   if constexpr (EPI == EPI_LOSS || EPI == EPI_LOSS_RES || EPI == EPI_LOSS_BLOCK) {
-    __shared__ float sred[NW];
+    // past the strips: a second LDS object would make the compiler wait for
+    // every copy in flight before each of the main loop's LDS reads
+    float* sred = scratch + NW * 32 * WN;
     for (int msk = 32; msk >= 1; msk >>= 1) lsum += __shfl_xor(lsum, msk, 64);
     if (lane == 0) sred[wave] = lsum;
     __syncthreads();
@@ -780,7 +818,8 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// Ping-pong main loop for single products on 256 x 256 or 256 x 128 tiles.
+// Ping-pong main loop for products on 256 x 128 tiles, and on 256 x 256 tiles
+// where K % 64 == 32.
 // Eight wavefronts in two groups of four, one wavefront of each group per
 // SIMD.  The groups alternate between an MFMA phase on fragments held in
 // registers and a memory phase (the next stage's fragments from LDS, this
@@ -814,7 +853,9 @@ __device__ __forceinline__ int pp_chunk(int row, int kc) {
 // reads, 4 k-rows apart, make the fragment.
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
-__device__ __forceinline__ bf16x8 tr_fragment(const char* stage, int off_lo, int off_hi) {
+// (restrict: the reads then carry alias information; without any the compiler
+// puts a wait for every copy in flight, vmcnt(0), in front of each read.)
+__device__ __forceinline__ bf16x8 tr_fragment(const char* __restrict__ stage, int off_lo, int off_hi) {
   const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(stage + off_lo));
   const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(stage + off_hi));
   const v4i16 both[2] = {lo, hi};
@@ -999,6 +1040,221 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
   epilogue<BM, BN, EPI, WM, WN, 8>(p, acc, m0, n0, wm, wn, lane, wave, tid, reinterpret_cast<float*>(smem));
 }
 
+// ---------------------------------------------------------------------------
+// Main loop for 256 x 256 tiles with K a multiple of 64: four wavefronts, one
+// per SIMD, each a 128 x 128 tile of v_mfma_f32_16x16x32_bf16 (256
+// accumulator registers), 64-deep stages (128-byte rows) in two LDS buffers.
+//
+// Why this shape.  Per 64-deep stage the four wavefronts read 128 KB of
+// fragments and the copies write 64 KB, 96 B per clock at full MFMA rate
+// against the 128 the LDS serves; eight wavefronts of 128 x 64 would need all
+// 128.  A copy of a whole 128-byte line per row keeps twice the bytes in
+// flight per request of a 64-byte one, and the 16 x 16 x 32 form moves half
+// the accumulator bytes per flop of 32 x 32 x 16, which counts where the
+// clock follows the power.
+//
+// With one wavefront per SIMD every instruction that cannot issue idles the
+// matrix core, so the order is fixed instruction by instruction (n counts the
+// stage's 128 MFMAs; the MFMAs are asm so that the accumulators stay where
+// they are, and scheduling barriers hold the rest between them):
+//   n = 0 ..      fragments of the stage's second half, one per two MFMAs;
+//   n = kBar1     they are in registers (and every wavefront's are: barrier),
+//                 so the copies of stage k + 2 into this buffer start, one
+//                 per six MFMAs;
+//   n = kBar2     stage k + 1 has landed (barrier), its first-half fragments
+//                 follow, one per three MFMAs.
+// Copies at one per four MFMAs or in bursts make the wavefronts wait for the
+// address path (1.43 against 1.48 PFLOP/s); the compiler's own order copied
+// the accumulators about and reached 1.04.
+// Measured (28672 x 4096 x 8192, 4096 x 4096 x 11008, 8192 x 4096 x 22016):
+// 1.52, 1.49, 1.48 PFLOP/s against 1.25, 1.19, 1.14 with the ping-pong kernel
+// (matrix cores busy 79% of the cycles against 56%).  The products equal the
+// 32 x 32 x 16 kernels' bit for bit.
+//
+// K-slow operands: a stage is 64 k-rows of 256 columns, chunk c of k-row r in
+// slot c ^ 4 (r & 3) as in the ping-pong kernel, fragments by two transpose
+// reads of four k-rows each.
+// ---------------------------------------------------------------------------
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(const F& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+__device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const uint16_t* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, -1, 0x00020000);
+}
+
+template <int EPI, bool TA = false, bool TB = false>
+__global__ __launch_bounds__(256, 1) void gemm_w4_kernel(GemmArgs p) {
+  select_batch(p);
+  constexpr int BM = 256, BN = 256, BK = 64;
+  constexpr int F = 8;                       // 16-row fragments per operand and wavefront
+  constexpr int PW = 16;                     // 1 KB copies per wavefront and stage
+  constexpr int kRead1 = 2, kBar1 = 36, kCopy = 6, kBar2 = 80, kRead2 = 3;
+  constexpr int kMid = (kBar2 - kBar1 + kCopy - 1) / kCopy;  // copies of stage k + 2 issued before kBar2
+  static_assert(15 * kRead1 < kBar1 && kBar1 <= 64 && kBar2 >= 64 && kBar2 + 15 * kRead2 < 128, "read slots");
+  static_assert(kBar1 + (PW - 1) * kCopy < 128, "a stage's copies are issued within one stage");
+  __shared__ uint4 smem[2 * (BM + BN) * 8];
+  uint4 (*sA)[BM * 8] = reinterpret_cast<uint4 (*)[BM * 8]>(smem);
+  uint4 (*sB)[BN * 8] = reinterpret_cast<uint4 (*)[BN * 8]>(smem + 2 * BM * 8);
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  int tm, tn;
+  tile_of<4>(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, tm, tn);
+  const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
+  const int64_t K = p.K;
+  // causal structure (uniform per workgroup, before any barrier)
+  if (p.causal == 1 && n0 >= m0 + BM) return;
+  const int64_t kb = p.causal == 3 ? m0 : 0;
+  const int64_t ke = p.causal == 2 ? min(K, m0 + BM) : K;
+  const int nk = int((ke - kb) / BK);
+
+  // Copy j < 8 of a wavefront is 1 KB block 8 wave + j of A's stage, j >= 8 of
+  // B's.  Lane l fills slot l of the block: row 8 blk + l / 8, slot l % 8,
+  // holding chunk pp_chunk(row, l % 8), or for a K-slow operand k-row
+  // 2 blk + l / 32, slot l % 32, holding chunk (l % 32) ^ 4 (k-row & 3).  Rows
+  // and columns past the matrix come from its last ones and are masked at the
+  // store.  voff: bytes from the operand's stage base, below 2^32 (checked on
+  // the host); the base moves by step bytes per stage.
+  const uint16_t* baseA = p.A + (TA ? kb * p.M : m0 * K + kb);
+  const uint16_t* baseB = p.B + (TB ? kb * p.N : EPI == EPI_SWIGLU ? n0 / 2 * K : n0 * K + kb);
+  const uint16_t* baseU = EPI == EPI_SWIGLU ? p.swiglu.Wu + n0 / 2 * K : nullptr;
+  const int64_t stepA = TA ? BK * p.M : BK, stepB = TB ? BK * p.N : BK;
+  uint32_t voff[PW];
+#pragma unroll
+  for (int j = 0; j < PW; ++j) {
+    const bool a = j < 8;
+    const int blk = wave * 8 + (j & 7);
+    if (a ? TA : TB) {
+      const int kr = blk * 2 + (lane >> 5);
+      const int c = (lane & 31) ^ (4 * (kr & 3));
+      const int64_t ext = a ? p.M : p.N;
+      voff[j] = uint32_t((kr * ext + min((a ? m0 : n0) + 8 * c, ext - 8)) * 2);
+    } else {
+      const int row = blk * 8 + (lane >> 3);
+      const int kc = pp_chunk<BK>(row, lane & 7);
+      int64_t r;  // row from the operand's base
+      if (a) r = min(m0 + row, p.M - 1) - m0;
+      else if (EPI == EPI_SWIGLU)  // interleaved 32-row blocks of W_g and W_u rows
+        r = min(n0 / 2 + 32 * (row >> 6) + (row & 31), p.swiglu.I - 1) - n0 / 2;
+      else r = min(n0 + row, p.N - 1) - n0;
+      voff[j] = uint32_t((r * K + kc * 8) * 2);
+    }
+  }
+  // copy jj of a stage, A and B blocks in turn
+  auto copy = [&](int st, const uint16_t* pa, const uint16_t* pb, const uint16_t* pu, int jj) {
+    const int j = (jj >> 1) + (jj & 1) * 8;
+    const int blk = wave * 8 + (j & 7);
+    uint4* dst = j < 8 ? &sA[st][blk * 64] : &sB[st][blk * 64];
+    // SiLU product: 8-row blocks 0 .. 3 of each 64 rows are W_g's, 4 .. 7 W_u's
+    const uint16_t* base = j < 8 ? pa : (EPI == EPI_SWIGLU && (j & 4)) ? pu : pb;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base), (lds_void*)dst, 16, voff[j], 0, 0, 0);
+  };
+
+  f32x4 acc[F][F];
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // Fragments: lane l holds row l % 16 of the 16, k 8 (l / 16) .. + 7 of the
+  // 32-deep half s.
+  const int lc = lane & 15, lq = lane >> 4;
+  const int swz = (lc >> 1) & 7;
+  const int offA[2] = {(wm * 128 + lc) * 8 + (lq ^ swz), (wm * 128 + lc) * 8 + ((4 + lq) ^ swz)};
+  const int offB[2] = {(wn * 128 + lc) * 8 + (lq ^ swz), (wn * 128 + lc) * 8 + ((4 + lq) ^ swz)};
+  // K-slow: byte offset of the 8 bytes this lane addresses for fragment i,
+  // half 0, first four k-rows (the next four 2048 bytes on, half 1 16384)
+  auto slow_off = [&](int w, int i) {
+    const int kr = 8 * lq + (lc >> 2);
+    const int chunk = w * 16 + 2 * i + ((lc & 3) >> 1);
+    return kr * 512 + ((chunk ^ (4 * (kr & 3))) << 4) + (lc & 1) * 8;
+  };
+  int toA[F], toB[F];
+#pragma unroll
+  for (int i = 0; i < F; ++i) {
+    toA[i] = TA ? slow_off(wm, i) : 0;
+    toB[i] = TB ? slow_off(wn, i) : 0;
+  }
+  bf16x8 fa[2][F], fb[2][F];
+  // read q of half s, in the order the MFMAs need them: B 0, A 0, B 1 .. 7, A 1 .. 7
+  auto read = [&](int st, int s, int q) {
+    if (q == 0 || (q >= 2 && q <= F)) {
+      const int j = q == 0 ? 0 : q - 1;
+      if constexpr (TB)
+        fb[s][j] = tr_fragment(reinterpret_cast<const char*>(&sB[st][0]), toB[j] + 16384 * s, toB[j] + 16384 * s + 2048);
+      else fb[s][j] = __builtin_bit_cast(bf16x8, sB[st][offB[s] + j * 128]);
+    } else {
+      const int i = q == 1 ? 0 : q - F;
+      if constexpr (TA)
+        fa[s][i] = tr_fragment(reinterpret_cast<const char*>(&sA[st][0]), toA[i] + 16384 * s, toA[i] + 16384 * s + 2048);
+      else fa[s][i] = __builtin_bit_cast(bf16x8, sA[st][offA[s] + i * 128]);
+    }
+  };
+
+  // stages past the last reload it (into a buffer that is not read again)
+  const uint16_t *a1 = baseA, *b1 = baseB, *u1 = baseU;  // stage k + 1
+#pragma unroll
+  for (int j = 0; j < PW; ++j) copy(0, a1, b1, u1, j);
+  if (nk > 1) {
+    a1 += stepA;
+    b1 += stepB;
+    if (EPI == EPI_SWIGLU) u1 += stepB;
+  }
+#pragma unroll
+  for (int j = 0; j < PW; ++j) copy(1, a1, b1, u1, j);
+  wait_vmcnt<PW>();  // this wavefront's share of stage 0
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int q = 0; q < 2 * F; ++q) read(0, 0, q);
+#pragma unroll 1
+  for (int k = 0; k < nk; ++k) {
+    const int st = k & 1;
+    const bool more = k + 2 < nk;
+    const uint16_t *a2 = a1 + (more ? stepA : 0), *b2 = b1 + (more ? stepB : 0);
+    const uint16_t* u2 = EPI == EPI_SWIGLU ? u1 + (more ? stepB : 0) : nullptr;
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, 128>([&](auto nc) {
+      constexpr int n = decltype(nc)::value;
+      if constexpr (n == kBar1) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront has read the whole stage
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (n == kBar2) {
+        wait_vmcnt<kMid>();  // this wavefront's share of stage k + 1
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      constexpr int s = n / 64, i = (n % 64) / F, j = n % F;
+      mfma16(acc[i][j], fa[s][i], fb[s][j]);
+      if constexpr (n < kBar1 && n % kRead1 == 0 && n / kRead1 < 2 * F) read(st, 1, n / kRead1);
+      if constexpr (n >= kBar1 && (n - kBar1) % kCopy == 0 && (n - kBar1) / kCopy < PW)
+        copy(st, a2, b2, u2, (n - kBar1) / kCopy);
+      if constexpr (n >= kBar2 && (n - kBar2) % kRead2 == 0 && (n - kBar2) / kRead2 < 2 * F)
+        read(st ^ 1, 0, (n - kBar2) / kRead2);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    a1 = a2;
+    b1 = b2;
+    u1 = u2;
+  }
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last MFMAs have written their registers
+  wait_vmcnt<0>();   // the reloads past the end have landed
+  __syncthreads();   // every wave is past its last operand read: the stages become epilogue scratch
+  epilogue<BM, BN, EPI, 128, 128>(p, acc, m0, n0, wm, wn, lane, wave, tid, reinterpret_cast<float*>(smem));
+}
+
 template <int BM, int BN>
 static int tiles(int64_t M, int64_t N) {
   return int(((M + BM - 1) / BM) * ((N + BN - 1) / BN));
@@ -1024,26 +1280,40 @@ size_t gemm_workgroups(int64_t M, int64_t N, int /*epi*/) {
   }
 }
 
-// Products with K a multiple of 32 on 256-row tiles (single, batched or
-// causal): the ping-pong kernel; on 128-row tiles: the pipelined kernel; the
+// Whether 256 x 256 tiles go to the four-wavefront kernel: whole 64-deep
+// stages, and byte offsets within a stage below 2^32.  It is the faster one on
+// every shape measured (by 18-30%); K % 64 == 32 keeps the ping-pong kernel.
+static bool w4_takes(const GemmArgs& a, bool ta, bool tb) {
+  return a.K % 64 == 0 && a.K <= (int64_t(1) << 22) && (!ta || a.M <= (int64_t(1) << 24)) &&
+         (!tb || a.N <= (int64_t(1) << 24));
+}
+
+// 256 x 256 tiles on the four-wavefront kernel where it takes the shape, else
+// on the ping-pong kernel with WAVES_M wavefront rows.
+template <int EPI, int WAVES_M = 2, bool TA = false, bool TB = false>
+static void launch_256(const GemmArgs& a, dim3 grid, hipStream_t st) {
+  if (w4_takes(a, TA, TB))
+    hipLaunchKernelGGL((gemm_w4_kernel<EPI, TA, TB>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI, WAVES_M, 32, TA, TB>), grid, dim3(512), 0, st, a);
+}
+
+// Products with K a multiple of 32 on 256 x 256 tiles: launch_256; on 256 x
+// 128 tiles the ping-pong kernel; on 128-row tiles: the pipelined kernel; the
 // register-staged kernel (any K that is a multiple of 8) otherwise.
 template <int BM, int BN, int EPI>
 static void launch_epi(const GemmArgs& a, dim3 grid, hipStream_t st) {
-  if constexpr (BM == 256 && (BN == 256 || BN == 128)) {
-    if (a.K % 32 == 0) {
-      // 64-deep stages where 256 x 128 tiles allow them (three fit in LDS)
-      if constexpr (BN == 128) {
-        if (a.K % 64 == 0) {
-          hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI, 4, 64>), grid, dim3(512), 0, st, a);
-          return;
-        }
-      }
-      hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI>), grid, dim3(512), 0, st, a);
-      return;
-    }
+  if (a.K % 32 != 0) {
+    hipLaunchKernelGGL((gemm_nt_kernel<BM, BN, EPI>), grid, dim3(256), 0, st, a);
+  } else if constexpr (BM == 256 && BN == 256) {
+    launch_256<EPI>(a, grid, st);
+  } else if constexpr (BM == 256) {
+    // 64-deep stages where 256 x 128 tiles allow them (three fit in LDS)
+    if (a.K % 64 == 0) hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI, 4, 64>), grid, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI>), grid, dim3(512), 0, st, a);
+  } else {
+    hipLaunchKernelGGL((gemm_pipe_kernel<BM, BN, EPI, 4>), grid, dim3(256), 0, st, a);
   }
-  if (a.K % 32 == 0) hipLaunchKernelGGL((gemm_pipe_kernel<BM, BN, EPI, 4>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((gemm_nt_kernel<BM, BN, EPI>), grid, dim3(256), 0, st, a);
 }
 
 template <int BM, int BN>
@@ -1082,18 +1352,17 @@ hipError_t launch_gemm_ste(const GemmLaunch& q, int k, hipStream_t st) {
   a.ste = q.ste;
   a.bsa = a.bsb = a.bso = 0;
   a.causal = 0;
-  // ping-pong kernel (4 x 2 wave grid: 64 x 128 wave tiles) where the shape
-  // gives at least one 256 x 256 tile per CU: the epilogue's memory phase then
-  // runs on eight wavefronts per CU
+  // four-wavefront or ping-pong kernel (4 x 2 wave grid: 64 x 128 wave tiles)
+  // where the shape gives at least one 256 x 256 tile per CU
   if (tiles<256, 256>(q.M, q.N) >= 256) {
     a.tiles_m = int((q.M + 255) / 256);
     a.tiles_n = int((q.N + 255) / 256);
     const dim3 grid(unsigned(a.tiles_m * a.tiles_n));
     switch (k) {
-      case 1: hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI_STE + 1, 4>), grid, dim3(512), 0, st, a); break;
-      case 2: hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI_STE + 2, 4>), grid, dim3(512), 0, st, a); break;
-      case 3: hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI_STE + 3, 4>), grid, dim3(512), 0, st, a); break;
-      default: hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI_STE + 4, 4>), grid, dim3(512), 0, st, a); break;
+      case 1: launch_256<EPI_STE + 1, 4>(a, grid, st); break;
+      case 2: launch_256<EPI_STE + 2, 4>(a, grid, st); break;
+      case 3: launch_256<EPI_STE + 3, 4>(a, grid, st); break;
+      default: launch_256<EPI_STE + 4, 4>(a, grid, st); break;
     }
     return hipGetLastError();
   }
@@ -1109,16 +1378,21 @@ hipError_t launch_gemm_ste(const GemmLaunch& q, int k, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Products with an operand stored K-slow: the ping-pong kernel with 32-deep
-// stages on 256 x 256 tiles where there are at least 256 of them, on
+// Products with an operand stored K-slow: 256 x 256 tiles (launch_256) where
+// there are at least 256 of them, the ping-pong kernel with 32-deep stages on
 // 256 x 128 tiles otherwise.  K % 32 == 0, M % 8 == 0 when A is K-slow.
-template <int BM, int BN, int EPI>
+template <int BN, int EPI, bool TA, bool TB>
+static void launch_kslow_n(const GemmArgs& a, dim3 grid, hipStream_t st) {
+  if constexpr (BN == 256) launch_256<EPI, 2, TA, TB>(a, grid, st);
+  else hipLaunchKernelGGL((gemm_pp_kernel<256, BN, EPI, 4, 32, TA, TB>), grid, dim3(512), 0, st, a);
+}
+
+template <int BN, int EPI>
 static void launch_kslow(const GemmArgs& a, int ta, int tb, hipStream_t st) {
   const dim3 grid(unsigned(a.tiles_m * a.tiles_n));
-  constexpr int WMM = BN == 256 ? 2 : 4;
-  if (ta && tb) hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI, WMM, 32, true, true>), grid, dim3(512), 0, st, a);
-  else if (tb) hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI, WMM, 32, false, true>), grid, dim3(512), 0, st, a);
-  else hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI, WMM, 32, true, false>), grid, dim3(512), 0, st, a);
+  if (ta && tb) launch_kslow_n<BN, EPI, true, true>(a, grid, st);
+  else if (tb) launch_kslow_n<BN, EPI, false, true>(a, grid, st);
+  else launch_kslow_n<BN, EPI, true, false>(a, grid, st);
 }
 
 static hipError_t launch_gemm_kslow(const GemmLaunch& q, hipStream_t st) {
@@ -1136,22 +1410,21 @@ static hipError_t launch_gemm_kslow(const GemmLaunch& q, hipStream_t st) {
   const bool bf = q.epi == EPI_GRAD_BF16;
   if (q.epi == EPI_SWIGLU_BWD) {  // input-gradient product dH = E W_d: B K-slow, 256 x 256 tiles
     a.tiles_n = int((q.N + 255) / 256);
-    hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI_SWIGLU_BWD, 2, 32, false, true>),
-                       dim3(unsigned(a.tiles_m * a.tiles_n)), dim3(512), 0, st, a);
+    launch_256<EPI_SWIGLU_BWD, 2, false, true>(a, dim3(unsigned(a.tiles_m * a.tiles_n)), st);
     return hipGetLastError();
   }
   if (wide) {
-    if (bf) launch_kslow<256, 256, EPI_GRAD_BF16>(a, q.ta, q.tb, st);
-    else launch_kslow<256, 256, EPI_GRAD_F32>(a, q.ta, q.tb, st);
+    if (bf) launch_kslow<256, EPI_GRAD_BF16>(a, q.ta, q.tb, st);
+    else launch_kslow<256, EPI_GRAD_F32>(a, q.ta, q.tb, st);
   } else {
-    if (bf) launch_kslow<256, 128, EPI_GRAD_BF16>(a, q.ta, q.tb, st);
-    else launch_kslow<256, 128, EPI_GRAD_F32>(a, q.ta, q.tb, st);
+    if (bf) launch_kslow<128, EPI_GRAD_BF16>(a, q.ta, q.tb, st);
+    else launch_kslow<128, EPI_GRAD_F32>(a, q.ta, q.tb, st);
   }
   return hipGetLastError();
 }
 
-// Head-split products (EPI_HEADS*): 256 x 256 tiles on the ping-pong kernel
-// with a 4 x 2 wave grid (64 x 128 wave tiles: a wave holds whole heads).
+// Head-split products (EPI_HEADS*): 256 x 256 tiles with 128-column wave
+// tiles (a wave holds whole heads; ping-pong kernel: 4 x 2 wave grid).
 // K % 32 == 0, N % 128 == 0.
 static hipError_t launch_gemm_heads(const GemmLaunch& q, hipStream_t st) {
   GemmArgs a;
@@ -1163,16 +1436,13 @@ static hipError_t launch_gemm_heads(const GemmLaunch& q, hipStream_t st) {
   a.tiles_m = int((q.M + 255) / 256);
   a.tiles_n = int((q.N + 255) / 256);
   const dim3 grid(unsigned(a.tiles_m * a.tiles_n));
-  if (q.epi == EPI_HEADS_ROT)
-    hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI_HEADS_ROT, 4>), grid, dim3(512), 0, st, a);
-  else
-    hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI_HEADS, 4>), grid, dim3(512), 0, st, a);
+  if (q.epi == EPI_HEADS_ROT) launch_256<EPI_HEADS_ROT, 4>(a, grid, st);
+  else launch_256<EPI_HEADS, 4>(a, grid, st);
   return hipGetLastError();
 }
 
 // Gate and up products with the SiLU product (EPI_SWIGLU): 256 x 256 tiles
-// of the interleaved columns (128 rows of W each) on the ping-pong kernel
-// with the 2 x 4 wave grid.  K % 32 == 0, I % 32 == 0.
+// of the interleaved columns (128 rows of W each).  K % 32 == 0, I % 32 == 0.
 static hipError_t launch_gemm_swiglu(const GemmLaunch& q, hipStream_t st) {
   GemmArgs a;
   a.A = q.A; a.B = q.B; a.M = q.M; a.N = 2 * q.swiglu.I; a.K = q.K;
@@ -1182,8 +1452,7 @@ static hipError_t launch_gemm_swiglu(const GemmLaunch& q, hipStream_t st) {
   a.swiglu = q.swiglu;
   a.tiles_m = int((q.M + 255) / 256);
   a.tiles_n = int((a.N + 255) / 256);
-  hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI_SWIGLU>), dim3(unsigned(a.tiles_m * a.tiles_n)), dim3(512), 0, st,
-                     a);
+  launch_256<EPI_SWIGLU>(a, dim3(unsigned(a.tiles_m * a.tiles_n)), st);
   return hipGetLastError();
 }
 
