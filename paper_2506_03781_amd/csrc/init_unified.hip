@@ -271,19 +271,175 @@ __device__ __forceinline__ void build_table(float* raw, float* qs, uint8_t* cof,
   wave_lds_sync();
 }
 
+// ---------------------------------------------------------------------------
+// The round's mapping step for groups with a lane per level.
+//
+// The kernel is bound by vector issue (100% of the cycles), so the step counts
+// instructions.  Where neighbouring levels are separated by more than 2^-20 of
+// any distance that can occur, their distances from a weight stay apart after
+// rounding: there is no run of equal distances to walk back, and the nearest
+// level is one of the two around the weight.  A level of -infinity in front
+// and positions counted by add-with-carry leave 16 instructions and three LDS
+// operations per weight (28 and seven with the general search).  The levels'
+// order seldom changes between rounds: lane j evaluates the level of the code
+// that was j-th last time, and only an order that fails the separation test is
+// ranked again (16% of the calls at k = 4, g = 128).
+//
+// A weight's state between rounds is one word, read from a table by position:
+// bits 31 .. 32-K the code's bits inverted (bit K-1 first, so a shift brings
+// bit b's sign to bit 31), and at 4 n, for the n-th pair p < q of bits (row
+// order), whether bits p and q differ: eight words added give the lane's
+// disagreement counts of all pairs.
+// 4096 x 4096, k = 4, g = 128, G = 30, T = 15: 9.1 ms, against 13.3 ms with the
+// general table and search for every round.
+// ---------------------------------------------------------------------------
+template <int K>
+__device__ __forceinline__ uint32_t code_word(int c) {
+  uint32_t w = (uint32_t(~c) & ((1u << K) - 1u)) << (32 - K);
+#pragma unroll
+  for (int p = 0, n = 0; p < K; ++p)
+#pragma unroll
+    for (int q = p + 1; q < K; ++q, ++n) w |= uint32_t(((c >> p) ^ (c >> q)) & 1) << (4 * n);
+  return w;
+}
+
+template <int K>
+__device__ __forceinline__ uint32_t word_code(uint32_t w) {
+  return (~w) >> (32 - K);
+}
+
+// x with the sign of code bit b (+ when set) of word w; xs holds x's own sign
+// bit in every place (x's bits shifted right arithmetically by 31).
+template <int K>
+__device__ __forceinline__ float signed_by(float x, uint32_t wx, int b) {
+  return __builtin_copysignf(x, __uint_as_float(wx << (K - 1 - b)));
+}
+
+__device__ __forceinline__ uint32_t sign_fill(float x) { return uint32_t(int(__float_as_uint(x)) >> 31); }
+
+// One group's table in LDS: lv[1 + j] the level at position j, lv[0] =
+// -infinity; words[1 + j] the word of its code.
+struct StepTable {
+  float* lv;
+  uint32_t* words;
+};
+
+// Levels of the group at (al, zb) into the table.  jl: lane within the group
+// (lanes past the last level only vote); myc: code at this lane's position,
+// kept between calls; myq: its level; bound: at least |x| for every weight of
+// the group; skip: lane outside the matrix.  Returns (the same in every lane)
+// whether the levels of every group are well separated.
+template <int K>
+__device__ __forceinline__ bool step_table(const StepTable& t, const uint32_t* wordc, const float (&al)[K], float zb,
+                                           int jl, int& myc, float& myq, float bound, bool skip) {
+  constexpr int L = 1 << K;
+  auto level = [&](int c) {
+    float q = zb;
+#pragma unroll
+    for (int b = 0; b < K; ++b) q = ((c >> b) & 1) ? q + al[b] : q - al[b];
+    return q;
+  };
+  const bool last = jl >= L - 1 || skip;
+  // whether the next position's level (the next lane's: positions 0 .. L-1 lie
+  // in one row of 16 lanes) is far enough above
+  auto separated = [&](float q) {
+    const float nb = __builtin_bit_cast(
+        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, q), 0x101, 0xF, 0xF, true));
+    return __all((nb - q) > 0x1p-20f * (bound + fabsf(q)) || last) != 0;
+  };
+  float q = level(myc);
+  bool ok = separated(q);
+  if (!ok) {
+    // rank the levels by (value, code): rank = levels below, counted as
+    // q2 < q, or for smaller codes q2 < the float after q
+    const int b = jl & (L - 1);
+    const float r = level(b) + 0.0f;  // -0 becomes +0
+    const float up = __uint_as_float(__float_as_uint(r) + ((int(__float_as_uint(r)) >> 31) | 1));
+    if (jl < L) t.lv[1 + b] = r;
+    wave_lds_sync();
+    int rank = 0;
+#pragma unroll
+    for (int b2 = 0; b2 < L; ++b2) rank += t.lv[1 + b2] < (b2 < b ? up : r) ? 1 : 0;
+    if (jl < L) t.words[1 + rank] = uint32_t(b);
+    wave_lds_sync();
+    myc = int(t.words[1 + b]) & (L - 1);
+    wave_lds_sync();
+    if (jl < L) t.words[1 + b] = wordc[myc];
+    q = level(myc);
+    ok = separated(q);
+  }
+  myq = q;
+  if (jl < L) t.lv[1 + jl] = q;
+  wave_lds_sync();
+  return ok;
+}
+
+// pos = 2 pos + (x >= t)
+__device__ __forceinline__ void shift_in(int& pos, float x, float t) {
+  asm("v_cmp_ge_f32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(pos) : "v"(x), "v"(t) : "vcc");
+}
+
+// The words of N weights x(i): the levels at or below x among all but the last
+// counted by bisection (its first two steps from registers), then the nearer
+// of the two levels around x, the lower one on equal distances.
+template <int K, int N, typename X, typename Put>
+__device__ __forceinline__ void map_words(const StepTable& t, bool ok, const X& x, const Put& put) {
+  constexpr int L = 1 << K;
+  if (ok) {
+    const float* q = t.lv + 1;
+    const float tm = q[L / 2 - 1], tlo = q[K > 1 ? L / 4 - 1 : 0], thi = q[K > 1 ? 3 * L / 4 - 1 : 0];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float xi = x(i);
+      int pos = 0;
+      if constexpr (K == 1) {
+        shift_in(pos, xi, tm);
+      } else {
+        float t2;
+        asm("v_cmp_ge_f32_e32 vcc, %2, %3\n\t"
+            "v_cndmask_b32_e32 %1, %4, %5, vcc\n\t"
+            "v_cndmask_b32_e64 %0, 0, 1, vcc\n\t"
+            "v_cmp_ge_f32_e32 vcc, %2, %1\n\t"
+            "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+            : "=&v"(pos), "=&v"(t2)
+            : "v"(xi), "v"(tm), "v"(tlo), "v"(thi)
+            : "vcc");
+        if constexpr (K == 4) shift_in(pos, xi, q[4 * pos + 1]);
+        if constexpr (K >= 3) shift_in(pos, xi, q[2 * pos]);
+      }
+      const float da = xi - t.lv[pos], db = xi - t.lv[pos + 1];
+      asm("v_cmp_lt_f32_e64 vcc, |%1|, |%2|\n\tv_addc_co_u32_e32 %0, vcc, 0, %0, vcc"
+          : "+v"(pos)
+          : "v"(db), "v"(da)
+          : "vcc");
+      put(i, t.words[pos]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      float dist;
+      put(i, t.words[1 + nearest_full_k<K>(t.lv + 1, x(i), dist)]);
+    }
+  }
+}
+
 __host__ __device__ inline size_t init_wave_lds_bytes(int logg, int k) {
   const size_t e = (size_t(512) >> logg) << k;  // levels per wave
-  return (e * 9 + 15) & ~size_t(15);
+  return e * 12 + 16;  // tables of L + 1 levels and words (L >= 2), or raw and sorted levels and codes
 }
 
 template <int WDT, int K, int LOGG>
 __global__ __launch_bounds__(kThreads) void init_unified_kernel(InitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ uint32_t wordc[1 << K];
   constexpr int L = 1 << K;
   constexpr int lpg = 1 << (LOGG - 3);  // lanes per group
+  constexpr bool kStep = lpg >= L;      // a lane per level: mapping by thresholds
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int jl = lane & (lpg - 1);
+  if (threadIdx.x < L) wordc[threadIdx.x] = code_word<K>(threadIdx.x);
+  __syncthreads();
   const int64_t wave_off = (int64_t(blockIdx.x) * (kThreads / 64) + wave) * 512;
   if (wave_off >= a.N) return;  // whole wavefront past the end (no block barriers below)
   const int64_t off = wave_off + lane * 8;
@@ -297,6 +453,14 @@ __global__ __launch_bounds__(kThreads) void init_unified_kernel(InitArgs a) {
   float* raw = reinterpret_cast<float*>(wbase) + gl * L;
   float* qs = reinterpret_cast<float*>(wbase) + (gpw + gl) * L;
   uint8_t* cof = reinterpret_cast<uint8_t*>(wbase) + size_t(2 * gpw * L) * 4 + gl * L;
+  const StepTable tab{reinterpret_cast<float*>(wbase) + gl * (L + 1),
+                      reinterpret_cast<uint32_t*>(wbase) + (gpw + gl) * (L + 1)};
+  int myc = jl & (L - 1);
+  float myq = 0.0f;
+  if constexpr (kStep) {
+    if (jl < L) tab.words[1 + jl] = wordc[jl];
+    if (jl == 0) tab.lv[0] = -INFINITY;
+  }
 
   float w[8];
   if (active) {
@@ -367,91 +531,196 @@ __global__ __launch_bounds__(kThreads) void init_unified_kernel(InitArgs a) {
       }
     }
 
-    // Codes packed 4 per word: the C^T C counts and the fixed-point test use them.
-    uint32_t cw0 = pack4(code[0], code[1], code[2], code[3]);
-    uint32_t cw1 = pack4(code[4], code[5], code[6], code[7]);
-    for (int t = 0; t < a.T; ++t) {
-      // alpha <- (C^T C)^{-1} C^T (wbar - z_B)
-      float v[K];
+    float e2[8];
+    uint32_t c0 = 0, c1 = 0;
+    if constexpr (kStep) {
+      uint32_t wd[8], xs[8];
 #pragma unroll
-      for (int b = 0; b < K; ++b) {
-        float sx[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) sx[i] = ((code[i] >> b) & 1) ? x[i] : -x[i];
-        v[b] = group_sum<lpg>(sx);
+      for (int i = 0; i < 8; ++i) {
+        wd[i] = wordc[code[i]];
+        xs[i] = sign_fill(x[i]);
       }
-      int M[K][K];
-      {
-        // bit b of the lane's 8 codes, one bit per byte
-        uint32_t p0[K], p1[K];
+      const float bound = fmaxf(fabsf((wm / dl) + zu), fabsf((wM / dl) + zu));
+      for (int t = 0; t < a.T; ++t) {
+        // alpha <- (C^T C)^{-1} C^T (wbar - z_B)
+        float v[K];
+        {
+          uint32_t wx[8];
 #pragma unroll
-        for (int b = 0; b < K; ++b) {
-          p0[b] = (cw0 >> b) & 0x01010101u;
-          p1[b] = (cw1 >> b) & 0x01010101u;
-        }
+          for (int i = 0; i < 8; ++i) wx[i] = wd[i] ^ xs[i];
 #pragma unroll
-        for (int p = 0; p < K; ++p) {
-          M[p][p] = g;
+          for (int b = 0; b < K; ++b) {
+            float sx[8];
 #pragma unroll
-          for (int q = p + 1; q < K; ++q) {
-            const int dis = __builtin_popcount(p0[p] ^ p0[q]) + __builtin_popcount(p1[p] ^ p1[q]);
-            M[p][q] = g - 2 * group_reduce<lpg>(dis, AddI());
-            M[q][p] = M[p][q];
+            for (int i = 0; i < 8; ++i) sx[i] = signed_by<K>(x[i], wx[i], b);
+            v[b] = group_sum<lpg>(sx);
           }
         }
-      }
-      if constexpr (lpg >= K * (K + 1) / 2) solve_alpha_dist<K, lpg>(M, v, al, jl, lane);
-      else solve_alpha<K>(M, v, al);
+        int M[K][K];
+        M[0][0] = g;
+        if constexpr (K > 1) {
+          // the lane's counts (4-bit fields, at most 8), then in 8-bit fields
+          // over 16 lanes (at most 128), the rest one by one
+          uint32_t sum = wd[0];
+#pragma unroll
+          for (int i = 1; i < 8; ++i) sum += wd[i];
+          int ev = int(sum & 0x000F0F0Fu), od = int((sum >> 4) & 0x000F0F0Fu);
+          constexpr int kRow = lpg < 16 ? lpg : 16;
+          ev = group_reduce<kRow>(ev, AddI());
+          if constexpr (K > 2) od = group_reduce<kRow>(od, AddI());
+#pragma unroll
+          for (int p = 0, n = 0; p < K; ++p) {
+            M[p][p] = g;
+#pragma unroll
+            for (int q = p + 1; q < K; ++q, ++n) {
+              int dis = (((n & 1) ? od : ev) >> (8 * (n >> 1))) & 0xFF;
+              if constexpr (lpg >= 32) dis += sibling<16>(dis);
+              if constexpr (lpg >= 64) dis += sibling<32>(dis);
+              M[p][q] = g - 2 * dis;
+              M[q][p] = M[p][q];
+            }
+          }
+        }
+        if constexpr (lpg >= K * (K + 1) / 2) solve_alpha_dist<K, lpg>(M, v, al, jl, lane);
+        else solve_alpha<K>(M, v, al);
 
-      // C <- nearest level's code
+        // C <- nearest level's code
+        const bool ok = step_table<K>(tab, wordc, al, zb, jl, myc, myq, bound, !active);
+        uint32_t diff = 0;
+        map_words<K, 8>(tab, ok, [&](int i) { return wbar[i]; },
+                        [&](int i, uint32_t nw) {
+                          diff |= nw ^ wd[i];
+                          wd[i] = nw;
+                        });
+
+        // z_B <- mean(wbar - C alpha), only with a one-point grid
+        const float zb_prev = zb;
+        if (a.G == 1) {
+          float dd[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            float ca = 0.0f;
+            const uint32_t cd = word_code<K>(wd[i]);
+#pragma unroll
+            for (int b = 0; b < K; ++b) ca = ((cd >> b) & 1u) ? ca + al[b] : ca - al[b];
+            dd[i] = wbar[i] - ca;
+          }
+          zb = group_sum<lpg>(dd) * inv_g;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            x[i] = wbar[i] - zb;
+            xs[i] = sign_fill(x[i]);
+          }
+        }
+
+        // Unchanged codes and shift make this state a fixed point of the round
+        // (the round is a deterministic function of C, z_B and, for a singular
+        // C^T C, alpha), so the remaining rounds would reproduce it exactly.
+        if (__all((diff == 0 && zb == zb_prev) || !active)) break;
+      }
+
+      // Candidate error ||w - Q*(w)||^2 with the forward's FULL mapping: the
+      // last round's codes, unless z_B moved after them or there was no round.
+      if (a.G == 1 || a.T == 0) {
+        const bool ok = step_table<K>(tab, wordc, al, zb, jl, myc, myq, bound, !active);
+        map_words<K, 8>(tab, ok, [&](int i) { return wbar[i]; }, [&](int i, uint32_t nw) { wd[i] = nw; });
+      }
+      if (jl < L) tab.lv[1 + myc] = myq;  // levels by code
+      wave_lds_sync();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t cb = word_code<K>(wd[i]);
+        if (i < 4) c0 |= cb << (8 * i);
+        else c1 |= cb << (8 * (i - 4));
+        const float what = dl * (tab.lv[1 + cb] - zu);
+        const float d = w[i] - what;
+        e2[i] = d * d;
+      }
+    } else {
+      // Codes packed 4 per word: the C^T C counts and the fixed-point test use them.
+      uint32_t cw0 = pack4(code[0], code[1], code[2], code[3]);
+      uint32_t cw1 = pack4(code[4], code[5], code[6], code[7]);
+      for (int t = 0; t < a.T; ++t) {
+        // alpha <- (C^T C)^{-1} C^T (wbar - z_B)
+        float v[K];
+#pragma unroll
+        for (int b = 0; b < K; ++b) {
+          float sx[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) sx[i] = ((code[i] >> b) & 1) ? x[i] : -x[i];
+          v[b] = group_sum<lpg>(sx);
+        }
+        int M[K][K];
+        {
+          // bit b of the lane's 8 codes, one bit per byte
+          uint32_t p0[K], p1[K];
+#pragma unroll
+          for (int b = 0; b < K; ++b) {
+            p0[b] = (cw0 >> b) & 0x01010101u;
+            p1[b] = (cw1 >> b) & 0x01010101u;
+          }
+#pragma unroll
+          for (int p = 0; p < K; ++p) {
+            M[p][p] = g;
+#pragma unroll
+            for (int q = p + 1; q < K; ++q) {
+              const int dis = __builtin_popcount(p0[p] ^ p0[q]) + __builtin_popcount(p1[p] ^ p1[q]);
+              M[p][q] = g - 2 * group_reduce<lpg>(dis, AddI());
+              M[q][p] = M[p][q];
+            }
+          }
+        }
+        if constexpr (lpg >= K * (K + 1) / 2) solve_alpha_dist<K, lpg>(M, v, al, jl, lane);
+        else solve_alpha<K>(M, v, al);
+
+        // C <- nearest level's code
+        build_table<K>(raw, qs, cof, al, zb, jl, lpg);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          float dist;
+          code[i] = cof[nearest_full_k<K>(qs, wbar[i], dist)];
+        }
+        const uint32_t nw0 = pack4(code[0], code[1], code[2], code[3]);
+        const uint32_t nw1 = pack4(code[4], code[5], code[6], code[7]);
+
+        // z_B <- mean(wbar - C alpha), only with a one-point grid
+        const float zb_prev = zb;
+        if (a.G == 1) {
+          float dd[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            float ca = 0.0f;
+#pragma unroll
+            for (int b = 0; b < K; ++b) ca = ((code[i] >> b) & 1) ? ca + al[b] : ca - al[b];
+            dd[i] = wbar[i] - ca;
+          }
+          zb = group_sum<lpg>(dd) * inv_g;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) x[i] = wbar[i] - zb;
+        }
+
+        // Unchanged codes and shift make this state a fixed point of the round
+        // (the round is a deterministic function of C, z_B and, for a singular
+        // C^T C, alpha), so the remaining rounds would reproduce it exactly.
+        const bool same = (nw0 == cw0) & (nw1 == cw1) & (zb == zb_prev);
+        cw0 = nw0;
+        cw1 = nw1;
+        if (__all(same || !active)) break;
+      }
+
+      // Candidate error ||w - Q*(w)||^2 with the forward's FULL mapping.
       build_table<K>(raw, qs, cof, al, zb, jl, lpg);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         float dist;
-        code[i] = cof[nearest_full_k<K>(qs, wbar[i], dist)];
+        const int pos = nearest_full_k<K>(qs, wbar[i], dist);
+        const uint32_t cb = cof[pos];
+        if (i < 4) c0 |= cb << (8 * i);
+        else c1 |= cb << (8 * (i - 4));
+        const float what = dl * (qs[pos] - zu);
+        const float d = w[i] - what;
+        e2[i] = d * d;
       }
-      const uint32_t nw0 = pack4(code[0], code[1], code[2], code[3]);
-      const uint32_t nw1 = pack4(code[4], code[5], code[6], code[7]);
-
-      // z_B <- mean(wbar - C alpha), only with a one-point grid
-      const float zb_prev = zb;
-      if (a.G == 1) {
-        float dd[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          float ca = 0.0f;
-#pragma unroll
-          for (int b = 0; b < K; ++b) ca = ((code[i] >> b) & 1) ? ca + al[b] : ca - al[b];
-          dd[i] = wbar[i] - ca;
-        }
-        zb = group_sum<lpg>(dd) * inv_g;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = wbar[i] - zb;
-      }
-
-      // Unchanged codes and shift make this state a fixed point of the round
-      // (the round is a deterministic function of C, z_B and, for a singular
-      // C^T C, alpha), so the remaining rounds would reproduce it exactly.
-      const bool same = (nw0 == cw0) & (nw1 == cw1) & (zb == zb_prev);
-      cw0 = nw0;
-      cw1 = nw1;
-      if (__all(same || !active)) break;
-    }
-
-    // Candidate error ||w - Q*(w)||^2 with the forward's FULL mapping.
-    build_table<K>(raw, qs, cof, al, zb, jl, lpg);
-    float e2[8];
-    uint32_t c0 = 0, c1 = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float dist;
-      const int pos = nearest_full_k<K>(qs, wbar[i], dist);
-      const uint32_t cb = cof[pos];
-      if (i < 4) c0 |= cb << (8 * i);
-      else c1 |= cb << (8 * (i - 4));
-      const float what = dl * (qs[pos] - zu);
-      const float d = w[i] - what;
-      e2[i] = d * d;
     }
     const float e = group_sum<lpg>(e2);
     if (j == 1 || e < best_e) {
@@ -495,6 +764,14 @@ __global__ __launch_bounds__(kThreads) void init_unified_kernel(InitArgs a) {
 // its adjugate (|adj| <= g^3 < 2^42) and determinant are int64, exactly
 // converted (the determinant rounded) to fp64, and the products adj_ab v_b
 // round in fp64 and are added in ascending b, as written.
+//
+// With 16 wavefronts and one workgroup per CU the round was bound by its
+// barriers (six: three reductions of two each).  A round now has one exchange
+// with one barrier: the sums, the disagreement counts and whether the round
+// before changed anything travel together (a fixed point is then seen one
+// exchange later, with the same state), and two buffers alternate.  With the
+// mapping step above, 1024 rows of 11008 at k = 3, G = 30, T = 15: 7.3 ms
+// against 15.6.
 // ---------------------------------------------------------------------------
 // Pairwise sum of E values produced in index order (adjacent pairing): a
 // stack of partial sums, one per level.
@@ -524,49 +801,44 @@ __device__ __forceinline__ void tree_push_all(LaneTree<E>& t, const F& f) {
   }
 }
 
-// Pairwise sum of the N (a power of two) values r[0 .. N-1] in order.
-template <int N>
-__device__ __forceinline__ float pairwise_lds(const float* r) {
-  if constexpr (N == 1) return r[0];
-  else return pairwise_lds<N / 2>(r) + pairwise_lds<N / 2>(r + N / 2);
-}
-
-// Workgroup-wide pairwise sums of NV lane values (each lane already holds its
-// own subtree's sum), left in every lane; red holds NV values per wavefront.
-template <int NW, int NV, int CAP>
-__device__ __forceinline__ void block_tree(float (&t)[NV], float (&red)[CAP], int lane, int wave) {
-  static_assert(NV * NW <= CAP, "reduction buffer too small");
+// Exchange between the NW wavefronts of a workgroup of NF floats and NI
+// integers, each already summed over the wavefront's lanes: pairwise sums of
+// the floats in wavefront order and sums of the integers, in every lane.  Lane
+// l reads wavefront l % NW's values and a butterfly over NW lanes adds them (a
+// pairwise tree in order).  One barrier per exchange: the two buffers
+// alternate, and a buffer is written again only after the barrier of the
+// exchange in between, which every wavefront reaches after its reads.
+template <int NW, int CAP>
+struct Exchange {
+  uint32_t (*buf)[NW][CAP];  // [2][NW][CAP] words in LDS
+  int turn = 0;
+  int lane, wave;
+  template <int NF, int NI>
+  __device__ __forceinline__ void sum(float (&f)[NF], int (&n)[NI]) {
+    static_assert(NF + NI <= CAP, "exchange buffer too small");
+    uint32_t(*b)[CAP] = buf[turn];
+    turn ^= 1;
+    if (lane == 0) {
 #pragma unroll
-  for (int v = 0; v < NV; ++v) t[v] = group_reduce<64>(t[v], AddF());
-  if (lane == 0) {
+      for (int i = 0; i < NF; ++i) b[wave][i] = __float_as_uint(f[i]);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) red[v * NW + wave] = t[v];
+      for (int i = 0; i < NI; ++i) b[wave][NF + i] = uint32_t(n[i]);
+    }
+    __syncthreads();
+    const uint32_t* r = b[lane & (NW - 1)];
+#pragma unroll
+    for (int i = 0; i < NF; ++i) f[i] = group_reduce<NW>(__uint_as_float(r[i]), AddF());
+#pragma unroll
+    for (int i = 0; i < NI; ++i) n[i] = group_reduce<NW>(int(r[NF + i]), AddI());
   }
-  __syncthreads();
-#pragma unroll
-  for (int v = 0; v < NV; ++v) t[v] = pairwise_lds<NW>(red + v * NW);
-  __syncthreads();
-}
-
-template <int NW, int NV, int CAP>
-__device__ __forceinline__ void block_isum(int (&t)[NV], int (&red)[CAP], int lane, int wave) {
-  static_assert(NV * NW <= CAP, "reduction buffer too small");
-#pragma unroll
-  for (int v = 0; v < NV; ++v) t[v] = group_reduce<64>(t[v], AddI());
-  if (lane == 0) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) red[v * NW + wave] = t[v];
+  // one float, already summed over a lane's values only
+  __device__ __forceinline__ float lane_sum(float v) {
+    float f[1] = {group_reduce<64>(v, AddF())};
+    int none[1] = {0};
+    sum(f, none);
+    return f[0];
   }
-  __syncthreads();
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    int s = 0;
-#pragma unroll
-    for (int q = 0; q < NW; ++q) s += red[v * NW + q];
-    t[v] = s;
-  }
-  __syncthreads();
-}
+};
 
 // alpha = (C^T C)^{-1} v for C^T C entries up to 2^14, spread over the lanes
 // of a wavefront as solve_alpha_dist: lane j < K (K + 1) / 2 computes one
@@ -624,18 +896,22 @@ __device__ __forceinline__ void solve_alpha64_dist(const int (&M)[K][K], const f
 template <int WDT, int K, int NW, int E>
 __global__ __launch_bounds__(NW * 64) void init_unified_big_kernel(InitArgs a, int g) {
   constexpr int L = 1 << K;
-  constexpr int NP = E / 4;  // packed code words per lane
-  __shared__ float tab_raw[NW][L], tab_qs[NW][L];
-  __shared__ uint8_t tab_cof[NW][L];
-  __shared__ float red[8 * NW];
-  __shared__ int redi[8 * NW];
+  constexpr int kCnt = (K * (K - 1) / 2 + 1) / 2;  // words of two 16-bit disagreement counts
+  __shared__ float tab_lv[NW][L + 1];
+  __shared__ uint32_t tab_words[NW][L + 1];
+  __shared__ uint32_t wordc[L];
+  __shared__ uint32_t xbuf[2][NW][8];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t gid = blockIdx.x;
   const int64_t goff = gid * int64_t(g);
   const int e0 = int(threadIdx.x) * E;  // first padded element of this lane
-  float* raw = tab_raw[wave];
-  float* qs = tab_qs[wave];
-  uint8_t* cof = tab_cof[wave];
+  const StepTable tab{tab_lv[wave], tab_words[wave]};
+  Exchange<NW, 8> ex{xbuf, 0, lane, wave};
+  int myc = lane & (L - 1);
+  float myq = 0.0f;
+  if (threadIdx.x < L) wordc[threadIdx.x] = code_word<K>(threadIdx.x);
+  if (lane < L) tab.words[1 + lane] = code_word<K>(lane);
+  if (lane == 0) tab.lv[0] = -INFINITY;
 
   float w[E];
 #pragma unroll
@@ -656,42 +932,38 @@ __global__ __launch_bounds__(NW * 64) void init_unified_big_kernel(InitArgs a, i
   for (int c = 0; c < E; c += 8)
     if (e0 + c < g) valid8 |= 1u << (c / 8);
 #define UQ_VALID(i) (((valid8 >> ((i) / 8)) & 1u) != 0u)
-  // A wavefront whose elements are all padding adds exact zeros to every sum
-  // and keeps code 0: it skips the per-element work and only joins the
-  // workgroup reductions.
+  // A wavefront whose elements are all padding adds exact zeros to every sum:
+  // it skips the per-element work and only joins the exchanges.  Padding
+  // elements of a live wavefront keep x = 0 and word 0 (plus sign, no
+  // disagreement), which add exact zeros too.
   const bool live = __builtin_amdgcn_readfirstlane(wave) * 64 * E < g;
 
-  float mm[2] = {INFINITY, -INFINITY};
+  float wm = INFINITY, wM = -INFINITY;
 #pragma unroll
   for (int i = 0; i < E; ++i)
     if (UQ_VALID(i)) {
-      mm[0] = fminf(mm[0], w[i]);
-      mm[1] = fmaxf(mm[1], w[i]);
+      wm = fminf(wm, w[i]);
+      wM = fmaxf(wM, w[i]);
     }
-  mm[0] = group_reduce<64>(mm[0], MinF());
-  mm[1] = group_reduce<64>(mm[1], MaxF());
+  wm = group_reduce<64>(wm, MinF());
+  wM = group_reduce<64>(wM, MaxF());
   if (lane == 0) {
-    red[wave] = mm[0];
-    red[NW + wave] = mm[1];
+    xbuf[1][wave][0] = __float_as_uint(wm);
+    xbuf[1][wave][1] = __float_as_uint(wM);
   }
   __syncthreads();
-  float wm = red[0], wM = red[NW];
-#pragma unroll
-  for (int q = 1; q < NW; ++q) {
-    wm = fminf(wm, red[q]);
-    wM = fmaxf(wM, red[NW + q]);
-  }
-  __syncthreads();
+  wm = group_reduce<NW>(__uint_as_float(xbuf[1][lane & (NW - 1)][0]), MinF());
+  wM = group_reduce<NW>(__uint_as_float(xbuf[1][lane & (NW - 1)][1]), MaxF());
 
   const float L1 = float(L - 1);
   const float zb0 = L1 * 0.5f;
   const float gf = float(g);
   float best_d = 1.0f, best_zu = 0.0f, best_zb = zb0, best_e = 0.0f, best_al[K];
-  uint32_t best_cw[NP];
+  uint32_t best_cw[E / 4];  // codes packed four to a word
 #pragma unroll
   for (int b = 0; b < K; ++b) best_al[b] = 0.0f;
 #pragma unroll
-  for (int q = 0; q < NP; ++q) best_cw[q] = 0u;
+  for (int q = 0; q < E / 4; ++q) best_cw[q] = 0u;
 
   for (int j = 1; j <= a.G; ++j) {
     const float gamma = float(j) / float(a.G);
@@ -701,149 +973,166 @@ __global__ __launch_bounds__(NW * 64) void init_unified_big_kernel(InitArgs a, i
     if (a.clip == 0) zu = -(wm / dl);
     else if (a.clip == 1) zu = L1 - (wM / dl);
     else zu = -((gamma * wm) / dl);
+    const float bound = fmaxf(fabsf((wm / dl) + zu), fabsf((wM / dl) + zu));
     float wbar[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) wbar[i] = (w[i] / dl) + zu;
     float zb = zb0;
 
-    // greedy start, one bit at a time (r recomputed from x and the bits so far)
+    // greedy start, one bit at a time
     float al[K];
-    uint32_t cw[NP];
+    uint32_t wd[E];  // state words
+    {
+      float r[E];
+      int code[E];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) cw[q] = 0u;
-#pragma unroll
-    for (int b = 0; b < K; ++b) {
-      float t[1] = {0.0f};
-      if (live) {
-        LaneTree<E> tr;
-        tree_push_all<E>(tr, [&](int i) {
-          float r = wbar[i] - zb;
-          for (int bb = 0; bb < b; ++bb) r = ((cw[i / 4] >> (8 * (i & 3) + bb)) & 1u) ? r - al[bb] : r + al[bb];
-          return UQ_VALID(i) ? fabsf(r) : 0.0f;
-        });
-        t[0] = tr.st[LaneTree<E>::LG];
+      for (int i = 0; i < E; ++i) {
+        r[i] = UQ_VALID(i) ? wbar[i] - zb : 0.0f;
+        code[i] = 0;
       }
-      block_tree<NW, 1>(t, red, lane, wave);
-      const float ai = t[0] / gf;
-      if (live) {
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-          float r = wbar[i] - zb;
-          for (int bb = 0; bb < b; ++bb) r = ((cw[i / 4] >> (8 * (i & 3) + bb)) & 1u) ? r - al[bb] : r + al[bb];
-          if (UQ_VALID(i) && r >= 0.0f) cw[i / 4] |= 1u << (8 * (i & 3) + b);
-        }
-      }
-      al[b] = ai;
-    }
-
-    for (int t = 0; t < a.T; ++t) {
-      // alpha <- (C^T C)^{-1} C^T (wbar - z_B)
-      float v[K];
 #pragma unroll
       for (int b = 0; b < K; ++b) {
-        v[b] = 0.0f;
+        float t = 0.0f;
         if (live) {
           LaneTree<E> tr;
-          tree_push_all<E>(tr, [&](int i) {
-            const float x = wbar[i] - zb;
-            const bool bit = (cw[i / 4] >> (8 * (i & 3) + b)) & 1u;
-            return UQ_VALID(i) ? (bit ? x : -x) : 0.0f;
-          });
-          v[b] = tr.st[LaneTree<E>::LG];
+          tree_push_all<E>(tr, [&](int i) { return UQ_VALID(i) ? fabsf(r[i]) : 0.0f; });
+          t = tr.st[LaneTree<E>::LG];
+        }
+        const float ai = ex.lane_sum(t) / gf;
+        if (live) {
+#pragma unroll
+          for (int i = 0; i < E; ++i) {
+            const bool plus = r[i] >= 0.0f;
+            code[i] |= int(plus) << b;
+            r[i] = plus ? r[i] - ai : r[i] + ai;
+          }
+        }
+        al[b] = ai;
+      }
+#pragma unroll
+      for (int i = 0; i < E; ++i) wd[i] = UQ_VALID(i) ? wordc[code[i]] : 0u;
+    }
+
+    int same = 0;  // the previous round changed nothing in this wavefront
+    for (int t = 0; t < a.T; ++t) {
+      // C^T (wbar - z_B) and the disagreement counts of this wavefront
+      float v[K];
+      int cnt[kCnt + 1];
+#pragma unroll
+      for (int b = 0; b < K; ++b) v[b] = 0.0f;
+#pragma unroll
+      for (int q = 0; q <= kCnt; ++q) cnt[q] = 0;
+      if (live) {
+        float x[E];
+        uint32_t wx[E];
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          x[i] = UQ_VALID(i) ? wbar[i] - zb : 0.0f;
+          wx[i] = wd[i] ^ sign_fill(x[i]);
+        }
+#pragma unroll
+        for (int b = 0; b < K; ++b) {
+          LaneTree<E> tr;
+          tree_push_all<E>(tr, [&](int i) { return signed_by<K>(x[i], wx[i], b); });
+          v[b] = group_reduce<64>(tr.st[LaneTree<E>::LG], AddF());
+        }
+        if constexpr (K > 1) {
+          // 4-bit fields over 8 weights, 8-bit ones over the lane and 4 lanes
+          // (at most 64), 16-bit ones over the wavefront (at most 1024)
+          int ev = 0, od = 0;
+#pragma unroll
+          for (int c = 0; c < E; c += 8) {
+            uint32_t sum = wd[c];
+#pragma unroll
+            for (int i = 1; i < 8; ++i) sum += wd[c + i];
+            ev += int(sum & 0x000F0F0Fu);
+            od += int((sum >> 4) & 0x000F0F0Fu);
+          }
+          ev = group_reduce<4>(ev, AddI());
+          od = group_reduce<4>(od, AddI());
+          // pairs 2 q and 2 q + 1 in the halves of cnt[q]
+#pragma unroll
+          for (int q = 0; q < kCnt; ++q) {
+            int c = ((ev >> (8 * q)) & 0xFF) | (((od >> (8 * q)) & 0xFF) << 16);
+            c += sibling<4>(c);
+            c += sibling<8>(c);
+            c += sibling<16>(c);
+            c += sibling<32>(c);
+            cnt[q] = c;
+          }
         }
       }
-      block_tree<NW, K>(v, red, lane, wave);
+      // a wavefront of padding agrees with everything
+      cnt[kCnt] = live ? same : int(t > 0);
+      ex.sum(v, cnt);
+      // Unchanged codes and shift in the whole group after the last round: a
+      // fixed point, which the remaining rounds would reproduce exactly.
+      if (cnt[kCnt] == NW) break;
       int M[K][K];
-      {
-        // disagreement counts of bit pairs p < q, in row-major order
-        constexpr int NPQ = K > 1 ? K * (K - 1) / 2 : 1;
-        int dis[NPQ];
-        dis[0] = 0;
-#pragma unroll
-        for (int p = 0, n = 0; p < K; ++p)
-#pragma unroll
-          for (int q = p + 1; q < K; ++q, ++n) {
-            int c = 0;
-#pragma unroll
-            for (int w4 = 0; w4 < NP; ++w4)
-              c += __builtin_popcount(((cw[w4] >> p) ^ (cw[w4] >> q)) & 0x01010101u);
-            dis[n] = c;
-          }
-        block_isum<NW, NPQ>(dis, redi, lane, wave);
+      M[0][0] = g;
+      if constexpr (K > 1) {
 #pragma unroll
         for (int p = 0, n = 0; p < K; ++p) {
           M[p][p] = g;
 #pragma unroll
           for (int q = p + 1; q < K; ++q, ++n) {
-            M[p][q] = g - 2 * dis[n];
+            M[p][q] = g - 2 * ((cnt[n >> 1] >> (16 * (n & 1))) & 0xFFFF);
             M[q][p] = M[p][q];
           }
         }
       }
       solve_alpha64_dist<K>(M, v, al, lane);
 
-      // C <- nearest level's code (padding keeps code 0)
-      uint32_t nw[NP];
-#pragma unroll
-      for (int q = 0; q < NP; ++q) nw[q] = 0u;
+      // C <- nearest level's code
+      uint32_t diff = 0;
       if (live) {
-        build_table<K>(raw, qs, cof, al, zb, lane, 64);
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-          if (UQ_VALID(i)) {
-            float dist;
-            nw[i / 4] |= uint32_t(cof[nearest_full_k<K>(qs, wbar[i], dist)]) << (8 * (i & 3));
-          }
-        }
+        const bool ok = step_table<K>(tab, wordc, al, zb, lane, myc, myq, bound, false);
+        map_words<K, E>(tab, ok, [&](int i) { return wbar[i]; },
+                        [&](int i, uint32_t nw) {
+                          nw = UQ_VALID(i) ? nw : 0u;
+                          diff |= nw ^ wd[i];
+                          wd[i] = nw;
+                        });
       }
       const float zb_prev = zb;
       if (a.G == 1) {
-        float tz[1] = {0.0f};
+        float tz = 0.0f;
         if (live) {
           LaneTree<E> tr;
           tree_push_all<E>(tr, [&](int i) {
-            const uint32_t code = (nw[i / 4] >> (8 * (i & 3))) & 0xFFu;
+            const uint32_t code = word_code<K>(wd[i]);
             float ca = 0.0f;
             for (int b = 0; b < K; ++b) ca = ((code >> b) & 1u) ? ca + al[b] : ca - al[b];
             return UQ_VALID(i) ? wbar[i] - ca : 0.0f;
           });
-          tz[0] = tr.st[LaneTree<E>::LG];
+          tz = tr.st[LaneTree<E>::LG];
         }
-        block_tree<NW, 1>(tz, red, lane, wave);
-        zb = tz[0] / gf;
+        zb = ex.lane_sum(tz) / gf;
       }
-      int same = 1;
-#pragma unroll
-      for (int q = 0; q < NP; ++q) same &= int(nw[q] == cw[q]);
-      same &= int(zb == zb_prev);
-#pragma unroll
-      for (int q = 0; q < NP; ++q) cw[q] = nw[q];
-      int st1[1] = {same};
-      block_isum<NW, 1>(st1, redi, lane, wave);
-      if (st1[0] == NW * 64) break;  // every lane at a fixed point (uniform)
+      same = __all(diff == 0 && zb == zb_prev) ? 1 : 0;
     }
 
-    // candidate error ||w - Q*(w)||^2 with the forward's FULL mapping
-    uint32_t cc[NP];
-#pragma unroll
-    for (int q = 0; q < NP; ++q) cc[q] = 0u;
-    float te[1] = {0.0f};
+    // candidate error ||w - Q*(w)||^2 with the forward's FULL mapping: the
+    // last round's codes, unless z_B moved after them or there was no round
+    float te = 0.0f;
     if (live) {
-      build_table<K>(raw, qs, cof, al, zb, lane, 64);
+      if (a.G == 1 || a.T == 0) {
+        const bool ok = step_table<K>(tab, wordc, al, zb, lane, myc, myq, bound, false);
+        map_words<K, E>(tab, ok, [&](int i) { return wbar[i]; },
+                        [&](int i, uint32_t nw) { wd[i] = UQ_VALID(i) ? nw : 0u; });
+      }
+      if (lane < L) tab.lv[1 + myc] = myq;  // levels by code
+      wave_lds_sync();
       LaneTree<E> tr;
       tree_push_all<E>(tr, [&](int i) {
         if (!UQ_VALID(i)) return 0.0f;
-        float dist;
-        const int pos = nearest_full_k<K>(qs, wbar[i], dist);
-        cc[i / 4] |= uint32_t(cof[pos]) << (8 * (i & 3));
-        const float what = dl * (qs[pos] - zu);
+        const float what = dl * (tab.lv[1 + word_code<K>(wd[i])] - zu);
         const float d = w[i] - what;
         return d * d;
       });
-      te[0] = tr.st[LaneTree<E>::LG];
+      te = tr.st[LaneTree<E>::LG];
     }
-    block_tree<NW, 1>(te, red, lane, wave);
-    const float e = te[0];
+    const float e = ex.lane_sum(te);
     if (j == 1 || e < best_e) {
       best_e = e;
       best_d = dl;
@@ -852,7 +1141,9 @@ __global__ __launch_bounds__(NW * 64) void init_unified_big_kernel(InitArgs a, i
 #pragma unroll
       for (int b = 0; b < K; ++b) best_al[b] = al[b];
 #pragma unroll
-      for (int q = 0; q < NP; ++q) best_cw[q] = cc[q];
+      for (int q = 0; q < E / 4; ++q)
+        best_cw[q] = pack4(word_code<K>(wd[4 * q]), word_code<K>(wd[4 * q + 1]), word_code<K>(wd[4 * q + 2]),
+                           word_code<K>(wd[4 * q + 3]));
     }
   }
 

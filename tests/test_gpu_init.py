@@ -109,6 +109,25 @@ def test_init_degenerate_groups():
         check(W, 4, 128, G, T, 2, wdt=torch.float32)
 
 
+@pytest.mark.parametrize("k,g", [(1, 8), (1, 16), (2, 16), (2, 32), (3, 32), (3, 64), (4, 64), (4, 128), (4, 512),
+                                 (3, 520), (4, 1024)])
+def test_init_separated_and_tied_levels(k, g):
+    """Groups on both sides of the mapping step's choices (a lane per level or
+    fewer; levels well separated, tied or out of order between rounds): smooth
+    weights, coarse grids with exact ties, few distinct values and one far
+    outlier, for each clipping strategy."""
+    rs = np.random.default_rng(100 * k + g)
+    C = 2 * g if g > 512 else 1024
+    W = (rs.standard_normal((6, C)) * 0.05).astype(F32)
+    W[1] = np.round(W[1] * 32) / 32
+    W[2] = rs.choice(np.array([-0.5, 0.25, 0.25 + 2.0 ** -8], F32), C)
+    W[3, ::g] = 40.0
+    W[4] = np.abs(W[4]) + F32(3.0)
+    for clip in (0, 1, 2):
+        check(W, k, g, 3, 6, clip, wdt=torch.float32)
+    check(W, k, g, 1, 4, 0, wdt=torch.float32)
+
+
 def test_init_uniform_levels_recovered():
     vals = (np.arange(8) * 0.5 - 1.75).astype(F32)
     W = np.tile(np.repeat(vals, 16), (4, 1)).astype(F32)
