@@ -19,7 +19,8 @@
 // the 16 subset sums of those 4 activations.  One lookup replaces 4
 // multiply-adds; the tables are built once per workgroup and shared by its
 // 256 rows (one row per lane).  Slabs write fp32 partial rows that a second
-// kernel sums in a fixed order (deterministic results).
+// kernel sums in a fixed order (deterministic results).  Larger batches and
+// small layers take the product on the matrix cores (bcq_mfma_kernel).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -92,12 +93,14 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct BcqArgs {
   const uint16_t* X;
-  const u32x4* planes;
+  const uint32_t* planes;
   const uint16_t* alpha16;
   const uint16_t* z16;
   float* out;  // Y [T][R] (one slab) or partials [slabs][T][R]
   int64_t R, C, nq, gpr;
-  int g, qps;
+  int64_t rb0;       // first row block of this launch (MFMA kernel)
+  int qps, qpg;      // quads per slab and per group
+  uint32_t qpg_inv;  // ceil(2^32 / qpg): q / qpg = (q qpg_inv) >> 32 while q qpg < 2^32 (both at most 2^15)
 };
 
 // One v_bfe_u32 (the compiler otherwise splits a field extract of a masked
@@ -152,8 +155,8 @@ __global__ __launch_bounds__(256) void bcq_matmul_kernel(BcqArgs a) {
   const int64_t R = a.R;
   const int64_t pstride = a.nq * R, astride = a.gpr * R;
   const int64_t rc = live ? r : R - 1;
-  const u32x4* pp = a.planes + q0 * R + rc;
-  const uint32_t qpg = uint32_t(a.g) >> 7;
+  const u32x4* pp = reinterpret_cast<const u32x4*>(a.planes) + q0 * R + rc;
+  const uint32_t qpg = uint32_t(a.qpg);
   const uint32_t j0 = uint32_t(q0) / qpg, rem0 = uint32_t(q0) - j0 * qpg;
   u32x4 pw[QPS][K];
   float al[QPS][K], zz[QPS];
@@ -252,121 +255,218 @@ __global__ __launch_bounds__(256) void bcq_matmul_kernel(BcqArgs a) {
   for (int t = 0; t < T; ++t) out[int64_t(t) * a.R + r] = acc[t];
 }
 
-// The same product for larger batches on MFMA (v_mfma_f32_32x32x16_bf16):
-// P_i = X B_i^T with B_i the 0 / 1 matrix of plane i (exact in bf16) and S =
-// X 1^T, per 128-column quad, then y += sum_i (2 alpha*_i) P_i + (z* -
-// sum_i alpha*_i) S as in the table kernel.  C[m][n] is token m, row n: lane
-// l supplies token l % 32 (zero past T) and the bits of row l % 32, both at
-// columns 16 s + 8 (l / 32) .. + 8 of k-step s, and holds row l % 32 for
-// tokens 4 (l / 32) + rr in accumulator slots rr < 4 (T <= 8).  Each of the
-// 4 wavefronts takes 32 RT rows (RT 32-row tiles) of the workgroup's 128 RT;
-// with RT = 2 the grid, slabs and partial rows are the table kernel's.  The bits of a
-// fragment (8 columns of one row and plane) come from one LDS read of a
-// 256-entry table, whatever T; the table kernel's lookups grow with T.
 typedef __bf16 bf16x8b __attribute__((ext_vector_type(8)));
-typedef float f32x16b __attribute__((ext_vector_type(16)));
+typedef float f32x4b __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_a8 __attribute__((aligned(8)));  // activations are 8-byte aligned
 
-// bits j of b (j < 8) as bf16 0.0 / 1.0 in element j: for each pair t of
-// bits, t * 0x8001 puts bit 0 at position 0 and bit 1 at position 16 (the
-// other partial products land at 1 and 15 and are masked off), and the
-// product with 0x3F80 (bf16 1.0) makes the two halves.
-__device__ __forceinline__ bf16x8b bits_bf16(uint32_t b) {
-  u32x4 d;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) d[j] = (((b >> (2 * j)) & 3u) * 0x8001u & 0x10001u) * 0x3F80u;
-  return __builtin_bit_cast(bf16x8b, d);
-}
+// The same product on MFMA (v_mfma_f32_16x16x32_bf16), for batches of four
+// rows on and for small layers.  Per 128-column quad and plane, with B_i the
+// plane's bits, the matrix cores sum columns' x b (tokens as M, 16 weight rows
+// as N) and y += 2 alpha*_i P_i + (z* - sum_i alpha*_i) S as above.
+//
+// What bounds it is vector issue: every weight bit becomes a 16-bit operand.  A
+// lane holds one 32-column word of a row and plane, and the columns of a
+// fragment may come in any order that the activations share, so dword e of
+// fragment s pairs columns b and b + 16, b = 15 - 4 s - e: with the word
+// shifted left by 4 s, their bits stand at 15 - e of the dword's two halves, and
+// one v_and_or_b32 makes both bf16 values, whatever the bit's position:
+//   e = 0  the sign:              1/2 - b
+//   e = 1  exponent bit 7:        -2 b (0 or -2; the activations are halved)
+//   e = 2  exponent bit 6:        -b   (-2^-64 for 0)
+//   e = 3  exponent bit 5:        -b   (-2^-32 for 0, 2^8 below fp32's rounding)
+// 16 and three shifts per word and plane, where a 256-entry table in LDS was
+// bound by its 16-byte reads.  The sums come as S_0 / 2 - P_i with S_0 the
+// activation sum of the sign columns; one more product with constant columns
+// gives S and S - S_0, and the kernel keeps y / 2 so that no factor is applied
+// twice:  y / 2 = sum [ z S / 2 - asum (S - S_0) / 2 - sum_i alpha*_i (S_0 / 2 - P_i) ].
+//
+// A wavefront takes 16 RT rows of its quads; the W wavefronts of a workgroup
+// split the quads of the same rows and add up in LDS in a fixed order, so that
+// most shapes need no partial rows and no second launch.  Each wavefront loads
+// its quad's activations once, coalesced, pairs and halves them and reads the
+// fragments back from its own LDS region (fragments loaded from memory touched
+// 64 lines an instruction and were the bound: 58 us).  With RT = 2 a plane is
+// one 8-byte load per lane, and v_permlane32_swap sorts words and parameters
+// to the two row tiles.
+// Measured (T = 8, g = 128): 28672 x 8192, k = 3: 38 us against 44 for the
+// table-expanded 32 x 32 x 16 form with partial rows; 8192 x 28672: 36 against
+// 44; 4096 x 4096, k = 4: 7.2 against 10.2 (one launch instead of two).
+// One 128-column quad of 16 RT rows as a wavefront loads it: plane words,
+// parameters (binary16) and this lane's 32 activations.
+template <int K, int RT>
+struct BcqQuad {
+  uint32_t w[K][RT];
+  uint16_t a[K], z;
+  u32x4 x[2];
+};
 
-template <int K, int QPS, int RT = 2>
-__global__ __launch_bounds__(256) void bcq_mfma_kernel(BcqArgs a, int T) {
-  // the 256 bytes as 8 bf16 each, built once: one LDS read per 8 bits
-  __shared__ u32x4 tbl[256];
-  // the slab's activations, T rows of QPS * 128 bf16 with a 32-byte pad
-  // (the 16 fragments a k-step reads fall in distinct bank groups)
-  constexpr int XLD = QPS * 128 + 16;
-  __shared__ __attribute__((aligned(16))) uint16_t xs[8 * XLD];
-  tbl[threadIdx.x] = __builtin_bit_cast(u32x4, bits_bf16(threadIdx.x));
-  const int64_t q0 = int64_t(blockIdx.y) * QPS;
-  const int nqs = int(min<int64_t>(QPS, a.nq - q0));
-  {
-    const int per_row = nqs * 32;  // 8-byte chunks per activation row
-    for (int e = threadIdx.x; e < T * per_row; e += 256) {
-      const int t = e / per_row, c = e - t * per_row;
-      *reinterpret_cast<uint2*>(&xs[t * XLD + 4 * c]) =
-          *reinterpret_cast<const uint2*>(a.X + int64_t(t) * a.C + q0 * 128 + 4 * c);
-    }
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tok = lane & 31, hk = lane >> 5;
-  const int64_t R = a.R;
-  const int64_t rbase = int64_t(blockIdx.x) * (128 * RT) + wave * (32 * RT);
-  const int64_t astride = a.gpr * R;
-  const uint32_t qpg = uint32_t(a.g) >> 7;
-  bf16x8b ones;
+// Workgroup (bx, by): the 16 RT rows of row block rb0 + bx, quads qps by .. + qps - 1;
+// wavefront w takes every W-th of them.
+template <int K, int RT, int W>
+__global__ __launch_bounds__(64 * W) void bcq_mfma_kernel(BcqArgs a, int T) {
+  constexpr int ROWS = 16 * RT;
+  constexpr int XLD = 17;  // 16-byte chunks per token (16 and one of padding: 8 tokens in distinct banks)
+  __shared__ u32x4 xs[W][8 * XLD];
+  __shared__ float red[W][8][ROWS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, kg = lane >> 4;
+  const int64_t R = a.R, r0 = (a.rb0 + blockIdx.x) * ROWS;
+  // rows past R are loaded from the last one
+  const uint32_t row = uint32_t(min(r0 + n + (RT == 2 ? 16 * (kg >> 1) : 0), R - 1) - r0);
+  const int word = RT == 2 ? ((kg & 1) << 1) | (kg >> 1) : kg;  // of the quad's four, in the lane's fragments
+  const int64_t q_end = min<int64_t>(a.nq, int64_t(blockIdx.y + 1) * a.qps);
+  int64_t q = int64_t(blockIdx.y) * a.qps + wave;
+  // 32-bit lane offsets from uniform bases (the quad and the wavefront are
+  // uniform).  This lane loads columns 32 xw + 8 xc .. + 7 and the 8 sixteen
+  // on, of token xt (tokens past T repeat the last, unused).
+  const int xt = lane >> 3, xw = (lane >> 1) & 3, xc = lane & 1;
+  const uint32_t xoff = 2u * (uint32_t(min(xt, T - 1)) * uint32_t(a.C) + 32u * xw + 8u * xc);
+  u32x4* xput = &xs[wave][xt * XLD + 4 * xw + 2 * (1 - xc)];
+  const u32x4* xget = &xs[wave][(n & 7) * XLD + 4 * word];
+  const uint32_t woff = row * 16 + (RT == 2 ? 8 * (kg & 1) : 4 * kg), poff = row * 2;
+  auto at = [](const void* base, uint32_t off) { return static_cast<const char*>(base) + off; };
+
+  auto load = [&](BcqQuad<K, RT>& d, int64_t qq) {
+    const int64_t j = a.qpg == 1 ? qq : int64_t((uint64_t(qq) * a.qpg_inv) >> 32);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = __bf16(1.0f);
-  float y[RT][4];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) y[rt][rr] = 0.0f;
-  for (int qq = 0; qq < nqs; ++qq) {
-    const int64_t q = q0 + qq;
-    const int64_t j = int64_t(uint32_t(q) / qpg);
-    // this lane's activations for the quad's 8 k-steps (zero past T)
-    bf16x8b xa[8];
-    const u32x4* xr = reinterpret_cast<const u32x4*>(&xs[min(tok, T - 1) * XLD + qq * 128 + 8 * hk]);
-#pragma unroll
-    for (int st = 0; st < 8; ++st) {
-      const u32x4 v = xr[2 * st];
-      const u32x4 z4 = {0u, 0u, 0u, 0u};
-      xa[st] = __builtin_bit_cast(bf16x8b, tok < T ? v : z4);
-    }
-    f32x16b S = {};
-#pragma unroll
-    for (int st = 0; st < 8; ++st) S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[st], ones, S, 0, 0, 0);
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int64_t r = rbase + 32 * rt + tok;
-      const int64_t rc = r < R ? r : R - 1;
-      u32x4 w[K];
-      float al[K];
-#pragma unroll
-      for (int i = 0; i < K; ++i) {
-        w[i] = a.planes[(i * a.nq + q) * R + rc];
-        al[i] = f16_to_f32(a.alpha16[i * astride + j * R + rc]);
+    for (int i = 0; i < K; ++i) {
+      const uint32_t* pp = a.planes + ((i * a.nq + qq) * R + r0) * 4;
+      if constexpr (RT == 2) {
+        const uint2 v = *reinterpret_cast<const uint2*>(at(pp, woff));
+        d.w[i][0] = v.x;
+        d.w[i][1] = v.y;
+      } else {
+        d.w[i][0] = *reinterpret_cast<const uint32_t*>(at(pp, woff));
       }
-      const float zc0 = f16_to_f32(a.z16[j * R + rc]);
+      d.a[i] = *reinterpret_cast<const uint16_t*>(at(a.alpha16 + (i * a.gpr + j) * R + r0, poff));
+    }
+    d.z = *reinterpret_cast<const uint16_t*>(at(a.z16 + j * R + r0, poff));
+    const uint16_t* xq = a.X + qq * 128;
+    d.x[0] = *reinterpret_cast<const u32x4_a8*>(at(xq, xoff));
+    d.x[1] = *reinterpret_cast<const u32x4_a8*>(at(xq + 16, xoff));
+  };
+
+  // columns n even: 1/2 on every column, n odd: 1/2 on all but the sign slots
+  constexpr uint32_t HALF = 0x3F003F00u;
+  const u32x4 sums = {(n & 1) ? 0u : HALF, 0x3F803F80u, HALF, HALF};  // (slot 1 holds x / 2)
+  f32x4b y[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) y[t] = f32x4b{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // Bits as bf16 (the two halves of a dword at once): constants the compiler
+  // keeps in registers, so that (w & m) | c is one v_and_or_b32 (as literals
+  // they make it two instructions).
+  uint32_t m[4] = {0x80008000u, 0x40004000u, 0x20002000u, 0x10001000u};
+  uint32_t c[4] = {HALF, 0x80008000u, 0x9F809F80u, 0xAF80AF80u};
+  asm("" : "+s"(m[0]), "+s"(m[1]), "+s"(m[2]), "+s"(m[3]));
+  asm("" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
+
+  auto mul = [&](BcqQuad<K, RT>& d) {
+    // chunk s, dword e: columns b and b + 16 of the word, b = 15 - 4 s - e
+    bf16x8b xa[4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      u32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = (7 - 4 * h - e) >> 1;
+        v[e] = __builtin_amdgcn_perm(d.x[1][i], d.x[0][i], (e & 1) ? 0x05040100u : 0x07060302u);
+      }
+      const float lo = __uint_as_float(v[1] << 16) * 0.5f, hi = __uint_as_float(v[1] & 0xFFFF0000u) * 0.5f;
+      v[1] = __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+      xput[h] = v;
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): written (read by this wavefront only)
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) xa[s] = __builtin_bit_cast(bf16x8b, xget[s]);
+    f32x4b Sm = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      Sm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[s], __builtin_bit_cast(bf16x8b, sums), Sm, 0, 0, 0);
+    uint32_t al[K][RT], zz[RT];
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      al[i][0] = d.a[i];
+      if constexpr (RT == 2) {
+        const auto wv = __builtin_amdgcn_permlane32_swap(d.w[i][0], d.w[i][1], false, false);
+        d.w[i][0] = wv[0];
+        d.w[i][1] = wv[1];
+        const auto av = __builtin_amdgcn_permlane32_swap(d.a[i], d.a[i], false, false);
+        al[i][0] = av[0];
+        al[i][1] = av[1];
+      }
+    }
+    zz[0] = d.z;
+    if constexpr (RT == 2) {
+      const auto zv = __builtin_amdgcn_permlane32_swap(d.z, d.z, false, false);
+      zz[0] = zv[0];
+      zz[1] = zv[1];
+    }
+    f32x4b S, Se;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {  // quad_perm [0, 0, 2, 2] and [1, 1, 3, 3]
+      const int v = __float_as_int(Sm[r]);
+      S[r] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xA0, 0xF, 0xF, true));
+      Se[r] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xF5, 0xF, 0xF, true));
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const float z = f16_to_f32(uint16_t(zz[t]));
       float asum = 0.0f;
 #pragma unroll
       for (int i = 0; i < K; ++i) {
-        asum += al[i];
-        f32x16b P = {};
+        const float av = f16_to_f32(uint16_t(al[i][t]));
+        asum += av;
+        f32x4b P = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int st = 0; st < 8; ++st) {
-          const uint32_t byte = (w[i][st >> 1] >> (16 * (st & 1) + 8 * hk)) & 0xFFu;
-          P = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[st], __builtin_bit_cast(bf16x8b, tbl[byte]), P, 0, 0, 0);
+        for (int s = 0; s < 4; ++s) {
+          const uint32_t w = d.w[i][t] << (4 * s);
+          const u32x4 b = {(w & m[0]) | c[0], (w & m[1]) | c[1], (w & m[2]) | c[2], (w & m[3]) | c[3]};
+          P = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[s], __builtin_bit_cast(bf16x8b, b), P, 0, 0, 0);
         }
-        const float a2 = 2.0f * al[i];
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) y[rt][rr] += a2 * P[rr];
+        for (int r = 0; r < 4; ++r) y[t][r] = __builtin_fmaf(-av, P[r], y[t][r]);
       }
-      const float zc = zc0 - asum;
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) y[rt][rr] += zc * S[rr];
+      for (int r = 0; r < 4; ++r)
+        y[t][r] = __builtin_fmaf(z, S[r], __builtin_fmaf(-asum, Se[r], y[t][r]));
+    }
+  };
+
+  // The next quad's loads are in flight while one is multiplied; past the last
+  // they repeat it, so that no branch surrounds them (behind one, the compiler
+  // waits for every load in flight before each use).
+  if (q < q_end) {
+    BcqQuad<K, RT> d0, d1;
+    load(d0, q);
+    for (;;) {
+      const int64_t q1 = q + W, q2 = q1 + W;
+      load(d1, q1 < q_end ? q1 : q);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(d0);
+      if (q1 >= q_end) break;
+      load(d0, q2 < q_end ? q2 : q1);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(d1);
+      if (q2 >= q_end) break;
+      q = q2;
     }
   }
-  float* out = a.out + int64_t(blockIdx.y) * T * R;
+
+  if (kg < 2) {
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int64_t r = rbase + 32 * rt + tok;
-    if (r >= R) continue;
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int t = 4 * hk + rr;
-      if (t < T) out[int64_t(t) * R + r] = y[rt][rr];
-    }
+      for (int r = 0; r < 4; ++r) red[wave][4 * kg + r][16 * t + n] = 2.0f * y[t][r];
+  }
+  __syncthreads();
+  const int tok = threadIdx.x / ROWS, rr = threadIdx.x % ROWS;
+  if (tok < T && r0 + rr < R) {
+    float s = 0.0f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) s += red[w][tok][rr];
+    a.out[(int64_t(blockIdx.y) * T + tok) * R + r0 + rr] = s;
   }
 }
 
@@ -389,7 +489,9 @@ __global__ __launch_bounds__(256) void bcq_reduce_kernel(const float* __restrict
   Y[idx] = s;
 }
 
-// Quads per slab: the most (up to 4) that still give >= 512 workgroups.
+// Quads per slab of the table kernel, which sizes the workspace: the most (up to
+// 4) that still give >= 512 workgroups.  The MFMA kernel needs at most a quarter
+// of its slabs.
 int bcq_quads_per_slab(int64_t R, int64_t C) {
   const int64_t rb = (R + 255) / 256, nq = C / 128;
   for (int qps = 4; qps > 1; qps >>= 1)
@@ -419,48 +521,68 @@ static void launch_mm_t(const BcqArgs& a, int T, dim3 grid, hipStream_t st) {
   switch (T) {
     case 1: launch_mm_q<K, 1>(a, grid, st); break;
     case 2: launch_mm_q<K, 2>(a, grid, st); break;
-    case 3: launch_mm_q<K, 3>(a, grid, st); break;
-    case 4: launch_mm_q<K, 4>(a, grid, st); break;
-    case 5: launch_mm_q<K, 5>(a, grid, st); break;
-    case 6: launch_mm_q<K, 6>(a, grid, st); break;
-    case 7: launch_mm_q<K, 7>(a, grid, st); break;
-    default: launch_mm_q<K, 8>(a, grid, st); break;
+    default: launch_mm_q<K, 3>(a, grid, st); break;
   }
 }
 
 template <int K>
-static void launch_mfma_q(const BcqArgs& a, int T, dim3 grid, hipStream_t st) {
-  if (a.qps == 4) hipLaunchKernelGGL((bcq_mfma_kernel<K, 4>), grid, dim3(256), 0, st, a, T);
-  else if (a.qps == 2) hipLaunchKernelGGL((bcq_mfma_kernel<K, 2>), grid, dim3(256), 0, st, a, T);
-  else hipLaunchKernelGGL((bcq_mfma_kernel<K, 1>), grid, dim3(256), 0, st, a, T);
+static void launch_mfma(const BcqArgs& a, int T, int rt, int w, dim3 grid, hipStream_t st) {
+  if (rt == 1) hipLaunchKernelGGL((bcq_mfma_kernel<K, 1, 8>), grid, dim3(512), 0, st, a, T);
+  else if (w == 8) hipLaunchKernelGGL((bcq_mfma_kernel<K, 2, 8>), grid, dim3(512), 0, st, a, T);
+  else hipLaunchKernelGGL((bcq_mfma_kernel<K, 2, 16>), grid, dim3(1024), 0, st, a, T);
 }
 
 hipError_t launch_bcq_matmul(const BcqMatmulLaunch& p, hipStream_t st) {
   BcqArgs a;
+  a.rb0 = 0;
   a.X = p.X;
-  a.planes = reinterpret_cast<const u32x4*>(p.planes);
+  a.planes = p.planes;
   a.alpha16 = p.alpha16;
   a.z16 = p.z16;
   a.R = p.R;
   a.C = p.C;
   a.nq = p.C / 128;
   a.gpr = p.C / p.g;
-  a.g = p.g;
-  a.qps = bcq_quads_per_slab(p.R, p.C);
-  const int64_t slabs = (a.nq + a.qps - 1) / a.qps;
-  a.out = slabs == 1 ? p.Y : p.partials;
-  const dim3 grid(unsigned((p.R + 255) / 256), unsigned(slabs));
-  // tables for one to three batch rows, MFMA from four on (measured on the
-  // 70B and 4096 x 4096 layers: equal at four rows with k = 2, the MFMA form
-  // 1.9-2.2x faster at eight)
-  if (p.T >= 4) {
-    switch (p.k) {
-      case 1: launch_mfma_q<1>(a, p.T, grid, st); break;
-      case 2: launch_mfma_q<2>(a, p.T, grid, st); break;
-      case 3: launch_mfma_q<3>(a, p.T, grid, st); break;
-      default: launch_mfma_q<4>(a, p.T, grid, st); break;
+  a.qpg = p.g / 128;
+  a.qpg_inv = a.qpg > 1 ? uint32_t(((uint64_t(1) << 32) + a.qpg - 1) / a.qpg) : 0;
+  // Tables for one to three batch rows of layers above 21 M weights, where
+  // the bits are read at 4 TB/s (28672 x 8192, k = 3, one row: 23.5 us against
+  // 36 on MFMA; 2000 x 12288, k = 4: 10.1 against 12.0).  Below, the single launch
+  // counts (4096 x 4096, k = 4: 7.2 us against 9.6; 1000 x 4096: 7.1 against 9.6;
+  // 512 x 28672, two launches either way: 9.7 against 12.9), and from four rows
+  // on the MFMA form's time does not grow with the batch.
+  int64_t slabs;
+  if (p.T >= 4 || p.R * p.C <= (int64_t(5) << 22)) {
+    // 16 rows a workgroup where that gives more workgroups than 32 would leave
+    // CUs busy; 16 wavefronts where 32-row workgroups are few and rows long
+    // (8192 x 28672: 36 us against 38; 11008 x 4096: 12.1 against 10.9)
+    const int rt = p.R >= 8192 ? 2 : 1;
+    const int w = rt == 2 && p.R < 16384 && a.nq >= 128 ? 16 : 8;
+    const int64_t rb = (p.R + 16 * rt - 1) / (16 * rt);
+    // slabs only where the rows alone leave CUs idle and a wavefront would still
+    // have four quads (512 x 28672: 9.7 us with 7 slabs, 23 with one)
+    slabs = (256 + rb - 1) / rb;
+    if (slabs > a.nq / (4 * w)) slabs = a.nq / (4 * w);
+    if (slabs < 1) slabs = 1;
+    a.qps = int((a.nq + slabs - 1) / slabs);
+    slabs = (a.nq + a.qps - 1) / a.qps;
+    a.out = slabs == 1 ? p.Y : p.partials;
+    // a launch takes fewer than 2^32 threads
+    constexpr int64_t kMaxBlocks = int64_t(1) << 21;
+    for (a.rb0 = 0; a.rb0 < rb; a.rb0 += kMaxBlocks) {
+      const dim3 grid{unsigned(rb - a.rb0 < kMaxBlocks ? rb - a.rb0 : kMaxBlocks), unsigned(slabs), 1u};
+      switch (p.k) {
+        case 1: launch_mfma<1>(a, p.T, rt, w, grid, st); break;
+        case 2: launch_mfma<2>(a, p.T, rt, w, grid, st); break;
+        case 3: launch_mfma<3>(a, p.T, rt, w, grid, st); break;
+        default: launch_mfma<4>(a, p.T, rt, w, grid, st); break;
+      }
     }
   } else {
+    a.qps = bcq_quads_per_slab(p.R, p.C);
+    slabs = (a.nq + a.qps - 1) / a.qps;
+    a.out = slabs == 1 ? p.Y : p.partials;
+    const dim3 grid(unsigned((p.R + 255) / 256), unsigned(slabs));
     switch (p.k) {
       case 1: launch_mm_t<1>(a, p.T, grid, st); break;
       case 2: launch_mm_t<2>(a, p.T, grid, st); break;

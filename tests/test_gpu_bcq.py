@@ -91,7 +91,7 @@ def test_pack_bit_exact(R, C, k, g):
 
 
 # shapes: one slab (no partial sums), ragged rows (partial row blocks),
-# groups of 256 and of a whole row, 1 to 8 batch rows (tables up to 3, MFMA from 4)
+# groups of 256 and of a whole row, 1 to 8 batch rows (MFMA form)
 @pytest.mark.parametrize("T,R,C,k,g", [(1, 256, 512, 3, 128), (8, 300, 384, 4, 128), (3, 1000, 1280, 2, 256),
                                        (5, 64, 128, 1, 128), (2, 513, 2560, 4, 2560), (7, 4000, 1152, 3, 128),
                                        (4, 1000, 1280, 3, 256), (6, 513, 2560, 2, 2560)])
@@ -125,6 +125,15 @@ def test_matmul_partial_last_slab(T):
     """33 column quads at 2 per slab: the last slab holds one quad (table
     form at 3 batch rows, MFMA form at 6)."""
     sampled(T, 8192, 4224, 3, 128, 25, 48)
+
+
+# the MFMA form's dispatch: 16-row and 32-row workgroups with a ragged last one,
+# wavefronts with no quad, groups of 3 quads (divided by multiplication), column
+# slabs with partial sums, 16 wavefronts over long rows
+@pytest.mark.parametrize("T,R,C,k,g", [(1, 17, 128, 2, 128), (8, 15, 1152, 3, 384), (2, 33, 4224, 1, 1408),
+                                       (3, 40, 16512, 4, 384), (8, 8193, 2048, 2, 2048), (5, 8223, 16384, 1, 128)])
+def test_matmul_mfma_dispatch(T, R, C, k, g):
+    sampled(T, R, C, k, g, 31, min(R, 48))
 
 
 def test_matmul_full_size_attn4096():
