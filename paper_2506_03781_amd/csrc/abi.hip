@@ -181,6 +181,34 @@ size_t uniquan_recon_ws(int64_t T, int64_t R, int64_t C) {
   return uq::gemm_workgroups(R, T, uq::EPI_LOSS);
 }
 
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
+// Loss product f (partials of E^2 into f.partials, n of them), the loss and, if
+// asked for, the weight gradient 2 Et Xt^T, whose product then adds up the
+// partials too (one launch less) unless its output overlaps them or the loss.
+static uq_status loss_and_grad(const char* fn, const uq::GemmLaunch& f, size_t n, float* loss, const uint16_t* Xt,
+                               void* grad, int grad_dtype, hipStream_t st) {
+  if (uq_status s = hip_status(fn, uq::launch_gemm(f, st))) return s;
+  const int64_t R = f.M, T = f.N, C = f.K;
+  const size_t bytes = size_t(R) * size_t(C) * (grad_dtype == UQ_BF16 ? 2 : 4);
+  const bool fused =
+      grad != nullptr && !overlap(grad, bytes, f.partials, n * sizeof(float)) && !overlap(grad, bytes, loss, sizeof(float));
+  if (!fused)
+    if (uq_status s = hip_status(fn, uq::launch_reduce_loss(f.partials, int64_t(n), loss, st))) return s;
+  if (grad == nullptr) return UQ_OK;
+  uq::GemmLaunch b{static_cast<const uint16_t*>(f.out), Xt, R, C, T,
+                   grad_dtype == UQ_BF16 ? uq::EPI_GRAD_BF16 : uq::EPI_GRAD_F32, nullptr, grad, nullptr, 2.0f};
+  if (fused) {
+    b.red_in = f.partials;
+    b.red_n = int64_t(n);
+    b.red_out = loss;
+  }
+  return hip_status(fn, uq::launch_gemm(b, st));
+}
+
 uq_status uniquan_layer_recon(int64_t T, int64_t R, int64_t C, const uint16_t* X, const uint16_t* Xt,
                               const uint16_t* W_hat, const float* Yt, float* loss, uint16_t* Et_ws,
                               float* partials_ws, size_t partials_len, void* grad_W_hat, int grad_dtype,
@@ -198,13 +226,7 @@ uq_status uniquan_layer_recon(int64_t T, int64_t R, int64_t C, const uint16_t* X
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   uq::GemmLaunch f{W_hat, X, R, T, C, uq::EPI_LOSS, Yt, Et_ws, partials_ws, 1.0f};
-  if (uq_status s = hip_status(fn, uq::launch_gemm(f, st))) return s;
-  if (uq_status s = hip_status(fn, uq::launch_reduce_loss(partials_ws, int64_t(uniquan_recon_ws(T, R, C)), loss, st)))
-    return s;
-  if (grad_W_hat == nullptr) return UQ_OK;
-  uq::GemmLaunch b{Et_ws, Xt, R, C, T, grad_dtype == UQ_BF16 ? uq::EPI_GRAD_BF16 : uq::EPI_GRAD_F32,
-                   nullptr, grad_W_hat, nullptr, 2.0f};
-  return hip_status(fn, uq::launch_gemm(b, st));
+  return loss_and_grad(fn, f, uniquan_recon_ws(T, R, C), loss, Xt, grad_W_hat, grad_dtype, st);
 }
 
 uq_status uniquan_layer_recon_noalloc(int64_t T, int64_t R, int64_t C, const uint16_t* X, const uint16_t* Xt,
@@ -226,12 +248,7 @@ uq_status uniquan_layer_recon_noalloc(int64_t T, int64_t R, int64_t C, const uin
   if (uq_status s = hip_status(fn, uq::noalloc_scratch(&partials))) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
   uq::GemmLaunch f{W_hat, X, R, T, C, uq::EPI_LOSS, Yt, Et, partials, 1.0f};
-  if (uq_status s = hip_status(fn, uq::launch_gemm(f, st))) return s;
-  if (uq_status s = hip_status(fn, uq::launch_reduce_loss(partials, int64_t(need), loss, st))) return s;
-  if (grad_W_hat == nullptr) return UQ_OK;
-  uq::GemmLaunch b{Et, Xt, R, C, T, grad_dtype == UQ_BF16 ? uq::EPI_GRAD_BF16 : uq::EPI_GRAD_F32,
-                   nullptr, grad_W_hat, nullptr, 2.0f};
-  return hip_status(fn, uq::launch_gemm(b, st));
+  return loss_and_grad(fn, f, need, loss, Xt, grad_W_hat, grad_dtype, st);
 }
 
 size_t uniquan_recon_noalloc_max_partials(void) { return uq::kNoallocPartials; }

@@ -16,20 +16,22 @@
 //
 // Kernels (all bf16 MFMA with fp32 accumulation, v_mfma_f32_32x32x16_bf16
 // unless stated; the same sums in the same order either way):
-//   gemm_w4_kernel    the main one, for K % 64 == 0 on 256 x 256 tiles: four
-//                     wavefronts of 128 x 128 (v_mfma_f32_16x16x32_bf16), two
-//                     64-deep stages, the instruction order fixed by hand;
-//   gemm_pp_kernel    K % 32 == 0 on 256 x 128 tiles, and on 256 x 256 tiles
-//                     where K % 64 == 32: eight wavefronts in two groups that
-//                     alternate ("ping-pong") between an MFMA phase and a
-//                     memory phase (LDS fragment reads, global_load_lds copies
-//                     into a ring of 32- or 64-deep stages, exact vmcnt waits,
-//                     barriers);
+//   gemm_w4_kernel    the main one, on 256 x 256 tiles: four wavefronts of 128 x
+//                     128 (v_mfma_f32_16x16x32_bf16), two 64-deep stages, the
+//                     instruction order fixed by hand;
+//   gemm_pp_kernel    256 x 128 tiles, and 256 x 256 tiles of causal or K-slow
+//                     products that the first does not take: eight wavefronts
+//                     in two groups that alternate ("ping-pong") between an
+//                     MFMA phase and a memory phase (LDS fragment reads,
+//                     global_load_lds copies into a ring of 32- or 64-deep
+//                     stages, exact vmcnt waits, barriers);
 //   gemm_pipe_kernel  four wavefronts, the same direct-to-LDS stage ring, for
 //                     128 x 128 tiles (shapes too small to fill the GPU with
 //                     256-row tiles);
-//   gemm_nt_kernel    register-staged, 64-deep double-buffered slabs, for K
-//                     not a multiple of 32.
+//   gemm_nt_kernel    register-staged, 64-deep double-buffered slabs, for
+//                     256-row tiles with K below 64 and not a multiple of 32.
+// K is any multiple of 8: the direct-to-LDS kernels take a short first stage
+// (first_stage).  With K a multiple of 64 all give the same sums bit for bit.
 // The tile is the largest of 256x256, 256x128, 128x128 that still gives a
 // workgroup per compute unit.  Workgroups are renumbered so that each XCD
 // gets a contiguous run of tiles walked in groups of row-tiles, which keeps
@@ -69,6 +71,11 @@ struct GemmArgs {
   HeadsParams heads;
   SwigluParams swiglu;
   const float* Rres;  // EPI_LOSS_BLOCK, EPI_RESID: the residual added to the product
+  // EPI_GRAD_*: the loss partials of the product before, added up by one
+  // workgroup past the tiles (null: none)
+  const float* red_in;
+  int64_t red_n;
+  float* red_out;
 };
 
 // Operands and output of batch blockIdx.y.
@@ -513,6 +520,48 @@ __device__ __forceinline__ void epilogue(const GemmArgs& p, const Acc& acc, int6
   }
 }
 
+// Deterministic loss: fixed strided fp64 partial sums over 256 lanes, a fixed
+// xor butterfly within each wavefront, then the four wavefront totals in order.
+// All threads of the workgroup call it; sm: 32 bytes of LDS.
+__device__ __forceinline__ void reduce_loss(const float* __restrict__ partials, int64_t n, float* __restrict__ loss,
+                                            double* sm) {
+  const int tid = threadIdx.x;
+  double acc = 0.0;
+  if (tid < 256)
+    for (int64_t i = tid; i < n; i += 256) acc += double(partials[i]);
+  for (int msk = 32; msk >= 1; msk >>= 1) acc += __shfl_xor(acc, msk, 64);
+  if (tid < 256 && (tid & 63) == 0) sm[tid >> 6] = acc;
+  __syncthreads();
+  if (tid == 0) loss[0] = float((sm[0] + sm[1]) + (sm[2] + sm[3]));
+}
+
+// The workgroup past the tiles of a weight-gradient product adds up the loss
+// partials of the product before it: it runs beside the last tiles, where a
+// launch of its own took 5 us of the stream (layer step 4096 x 4096: 178 us).
+// True in that workgroup, which is then done.
+template <int EPI>
+__device__ __forceinline__ bool extra_workgroup(const GemmArgs& p, void* smem) {
+  if constexpr (EPI == EPI_GRAD_BF16 || EPI == EPI_GRAD_F32) {
+    if (int(blockIdx.x) >= p.tiles_m * p.tiles_n) {
+      reduce_loss(p.red_in, p.red_n, p.red_out, static_cast<double*>(smem));
+      return true;
+    }
+  }
+  return false;
+}
+
+// Source of the copies past the end of K (see first_stage).
+static __device__ uint4 zero_chunk;
+
+// K need not be a multiple of a kernel's stage depth: stage 0 is then the short
+// one, its first `first_stage` elements of each row from the operands and the
+// rest copied from zero_chunk, and the later stages are whole.  The short stage
+// comes first because the prologue issues it: the main loops stay as they are.
+__device__ __forceinline__ int first_stage(int64_t K, int BK) {
+  const int rem = int(K % BK);
+  return rem == 0 ? BK : rem;
+}
+
 template <int BM, int BN, int EPI>
 __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs p) {
   select_batch(p);
@@ -526,13 +575,14 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs p) {
   __shared__ uint4 smem[2 * (BM + BN) * 8];
   uint4 (*sA)[BM * 8] = reinterpret_cast<uint4 (*)[BM * 8]>(smem);
   uint4 (*sB)[BN * 8] = reinterpret_cast<uint4 (*)[BN * 8]>(smem + 2 * BM * 8);
+  if (extra_workgroup<EPI>(p, smem)) return;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   int tm, tn;
-  tile_of<(BM == 128 && BN == 128) ? 8 : 4>(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, tm, tn);
+  tile_of<4>(blockIdx.x, p.tiles_m * p.tiles_n, p.tiles_m, p.tiles_n, tm, tn);
   const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
   const int64_t K = p.K;
 
@@ -636,7 +686,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// Pipelined variant for K % 32 == 0: operands go straight from global memory
+// Pipelined variant: operands go straight from global memory
 // into a ring of S LDS stages (gfx950 global_load_lds_dwordx4, no register
 // staging), two stages ahead of the MFMAs; workgroup barriers carry no
 // memory fence (each wave waits only for its own loads of the stage it is
@@ -669,13 +719,14 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmArgs p) {
   __shared__ uint4 smem[S * (BM + BN) * 4];
   uint4 (*sA)[BM * 4] = reinterpret_cast<uint4 (*)[BM * 4]>(smem);
   uint4 (*sB)[BN * 4] = reinterpret_cast<uint4 (*)[BN * 4]>(smem + S * BM * 4);
+  if (extra_workgroup<EPI>(p, smem)) return;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   int tm, tn;
-  tile_of<(BM == 128 && BN == 128) ? 8 : 4>(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, tm, tn);
+  tile_of<(BM == 128 && BN == 128) ? 8 : 4>(blockIdx.x, p.tiles_m * p.tiles_n, p.tiles_m, p.tiles_n, tm, tn);
   const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
   const int64_t K = p.K;
   if (p.causal == 1 && n0 >= m0 + BM) return;  // whole tile above the diagonal (uniform per workgroup)
@@ -685,7 +736,9 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmArgs p) {
   // This lane's source for each of the wave's load instructions.  Lane l
   // fills LDS slot l of a 1 KB block: row 16*blk + l/4, slot l%4, which holds
   // chunk (l%4) ^ ((row>>1)&3) of that row.
-  const uint16_t* src[PER_WAVE];
+  const uint16_t* src[PER_WAVE];   // + 32 k: stage k >= 1
+  const uint16_t* src0[PER_WAVE];  // stage 0
+  const int first = first_stage(ke - kb, BK);
   int dst_off[PER_WAVE];
   bool isA[PER_WAVE];
 #pragma unroll
@@ -698,14 +751,17 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmArgs p) {
     isA[q] = a;
     const int64_t gr = a ? min(m0 + row, p.M - 1) : min(n0 + row, p.N - 1);
     src[q] = (a ? p.A : p.B) + gr * K + kb + kc * 8;
+    src0[q] = kc * 8 < first ? src[q] : reinterpret_cast<const uint16_t*>(&zero_chunk);
+    src[q] += first - BK;
     dst_off[q] = b * 64;
   }
+  auto copy = [&](const uint16_t* g, int stage, int q) {
+    uint4* dst = isA[q] ? &sA[stage][dst_off[q]] : &sB[stage][dst_off[q]];
+    __builtin_amdgcn_global_load_lds((glb_void*)g, (lds_void*)dst, 16, 0, 0);
+  };
   auto issue = [&](int stage, int64_t k0) {
 #pragma unroll
-    for (int q = 0; q < PER_WAVE; ++q) {
-      uint4* dst = isA[q] ? &sA[stage][dst_off[q]] : &sB[stage][dst_off[q]];
-      __builtin_amdgcn_global_load_lds((glb_void*)(src[q] + k0), (lds_void*)dst, 16, 0, 0);
-    }
+    for (int q = 0; q < PER_WAVE; ++q) copy(src[q] + k0, stage, q);
   };
 
   f32x16 acc[FM][FN];
@@ -762,9 +818,11 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmArgs p) {
     __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - 2, 0);   // MFMAs
   };
 
-  const int nk = int((ke - kb) / BK);
+  const int nk = int((ke - kb + BK - 1) / BK);
 #pragma unroll
-  for (int s = 0; s < S - 1; ++s)
+  for (int q = 0; q < PER_WAVE; ++q) copy(src0[q], 0, q);
+#pragma unroll
+  for (int s = 1; s < S - 1; ++s)
     if (s < nk) issue(s, int64_t(s) * BK);
   if (nk >= S - 1) wait_vmcnt<(S - 2) * PER_WAVE>();
   else wait_vmcnt<0>();
@@ -893,6 +951,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
   __shared__ uint4 smem[S * (BM + BN) * CPR];
   uint4 (*sA)[BM * CPR] = reinterpret_cast<uint4 (*)[BM * CPR]>(smem);
   uint4 (*sB)[BN * CPR] = reinterpret_cast<uint4 (*)[BN * CPR]>(smem + S * BM * CPR);
+  if (extra_workgroup<EPI>(p, smem)) return;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -902,7 +961,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
   const int wm = WAVES_M == 2 ? (qw >> 1) : qw;
   const int wn = WAVES_M == 2 ? ((qw & 1) * 2 + grp) : grp;
   int tm, tn;
-  tile_of<(BM == 128 && BN == 128) ? 8 : 4>(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, tm, tn);
+  tile_of<4>(blockIdx.x, p.tiles_m * p.tiles_n, p.tiles_m, p.tiles_n, tm, tn);
   const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
   const int64_t K = p.K;
   // causal structure (uniform per workgroup, before any barrier)
@@ -915,7 +974,11 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
   // K-slow operand's block is k-rows KPB blk .. (whole k-rows; slot l % CPK
   // of k-row r holds chunk (l % CPK) ^ 4 (r & 3)); columns past M or N are
   // loaded from the last chunk and masked at the store.
-  const uint16_t* src[PW];
+  // 64-deep stages: K need not be a multiple of 64 (see first_stage), but at
+  // least 64, so that the copies past the last stage reload a whole one.
+  const int first = BK == 64 ? first_stage(ke - kb, BK) : BK;
+  const uint16_t* src[PW];   // + k kstep: stage k (k >= 1 where stage 0 is short)
+  const uint16_t* src0[PW];  // stage 0
   int dst_off[PW];
   bool isA[PW];
   int64_t kstep[PW];  // elements per K stage
@@ -947,9 +1010,15 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
       const int64_t gr = a ? min(m0 + row, p.M - 1) : min(n0 + row, p.N - 1);
       src[j] = (a ? p.A : p.B) + gr * K + kb + kc * 8;
       kstep[j] = BK;
+      if (BK == 64) {
+        src0[j] = kc * 8 < first ? src[j] : reinterpret_cast<const uint16_t*>(&zero_chunk);
+        src[j] += first - BK;
+        continue;
+      }
     }
+    src0[j] = src[j];
   }
-  const int nk = int((ke - kb) / BK);
+  const int nk = int((ke - kb + BK - 1) / BK);
   auto issue = [&](int stage, int kstage) {
     const int64_t ks = int64_t(min(kstage, nk - 1));
 #pragma unroll
@@ -1009,7 +1078,11 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
   };
 
 #pragma unroll
-  for (int s = 0; s < S - 1; ++s) issue(s, s);
+  for (int j = 0; j < PW; ++j)
+    __builtin_amdgcn_global_load_lds((glb_void*)src0[j], (lds_void*)(isA[j] ? &sA[0][dst_off[j]] : &sB[0][dst_off[j]]), 16,
+                                     0, 0);
+#pragma unroll
+  for (int s = 1; s < S - 1; ++s) issue(s, s);
   wait_vmcnt<(S - 2) * PW>();  // this wavefront's share of stage 0
   __builtin_amdgcn_s_barrier();
   if (grp == 1) __builtin_amdgcn_s_barrier();
@@ -1104,20 +1177,22 @@ __global__ __launch_bounds__(256, 1) void gemm_w4_kernel(GemmArgs p) {
   __shared__ uint4 smem[2 * (BM + BN) * 8];
   uint4 (*sA)[BM * 8] = reinterpret_cast<uint4 (*)[BM * 8]>(smem);
   uint4 (*sB)[BN * 8] = reinterpret_cast<uint4 (*)[BN * 8]>(smem + 2 * BM * 8);
+  if (extra_workgroup<EPI>(p, smem)) return;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   int tm, tn;
-  tile_of<4>(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, tm, tn);
+  tile_of<4>(blockIdx.x, p.tiles_m * p.tiles_n, p.tiles_m, p.tiles_n, tm, tn);
   const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
   const int64_t K = p.K;
   // causal structure (uniform per workgroup, before any barrier)
   if (p.causal == 1 && n0 >= m0 + BM) return;
   const int64_t kb = p.causal == 3 ? m0 : 0;
   const int64_t ke = p.causal == 2 ? min(K, m0 + BM) : K;
-  const int nk = int((ke - kb) / BK);
+  const int nk = int((ke - kb + BK - 1) / BK);
+  const int first = first_stage(ke - kb, BK);
 
   // Copy j < 8 of a wavefront is 1 KB block 8 wave + j of A's stage, j >= 8 of
   // B's.  Lane l fills slot l of the block: row 8 blk + l / 8, slot l % 8,
@@ -1203,13 +1278,23 @@ __global__ __launch_bounds__(256, 1) void gemm_w4_kernel(GemmArgs p) {
   };
 
   // stages past the last reload it (into a buffer that is not read again)
-  const uint16_t *a1 = baseA, *b1 = baseB, *u1 = baseU;  // stage k + 1
+  // Stage 0, short where K is no multiple of 64 (see first_stage; at least 64
+  // here, so that it is not the one reloaded).
 #pragma unroll
-  for (int j = 0; j < PW; ++j) copy(0, a1, b1, u1, j);
+  for (int jj = 0; jj < PW; ++jj) {
+    const int j = (jj >> 1) + (jj & 1) * 8;
+    const bool a = j < 8;
+    const int blk = wave * 8 + (j & 7);
+    const int k0 = (a ? TA : TB) ? blk * 2 + (lane >> 5) : pp_chunk<BK>(blk * 8 + (lane >> 3), lane & 7) * 8;
+    const uint16_t* base = a ? baseA : (EPI == EPI_SWIGLU && (j & 4)) ? baseU : baseB;
+    const uint16_t* g = k0 < first ? base + (voff[j] >> 1) : reinterpret_cast<const uint16_t*>(&zero_chunk);
+    __builtin_amdgcn_global_load_lds((glb_void*)g, (lds_void*)(a ? &sA[0][blk * 64] : &sB[0][blk * 64]), 16, 0, 0);
+  }
+  const uint16_t *a1 = baseA, *b1 = baseB, *u1 = baseU;  // stage k + 1
   if (nk > 1) {
-    a1 += stepA;
-    b1 += stepB;
-    if (EPI == EPI_SWIGLU) u1 += stepB;
+    a1 += TA ? first * p.M : first;
+    b1 += TB ? first * p.N : first;
+    if (EPI == EPI_SWIGLU) u1 += first;
   }
 #pragma unroll
   for (int j = 0; j < PW; ++j) copy(1, a1, b1, u1, j);
@@ -1280,16 +1365,21 @@ size_t gemm_workgroups(int64_t M, int64_t N, int /*epi*/) {
   }
 }
 
-// Whether 256 x 256 tiles go to the four-wavefront kernel: whole 64-deep
-// stages, and byte offsets within a stage below 2^32.  It is the faster one on
-// every shape measured (by 18-30%); K % 64 == 32 keeps the ping-pong kernel.
+// Whether 64-deep stages take the shape: any K from 64 on (K-slow operands and
+// causal products, whose K range starts or ends at a tile, have their own
+// conditions on K).
+static bool deep_takes(const GemmArgs& a) { return a.K >= 64 && (a.causal == 0 || a.K % 64 == 0); }
+
+// Whether 256 x 256 tiles go to the four-wavefront kernel: 64-deep stages, and
+// byte offsets within a stage below 2^32.  It is the faster one on every shape
+// measured (by 18-30%).
 static bool w4_takes(const GemmArgs& a, bool ta, bool tb) {
-  return a.K % 64 == 0 && a.K <= (int64_t(1) << 22) && (!ta || a.M <= (int64_t(1) << 24)) &&
+  return deep_takes(a) && a.K <= (int64_t(1) << 22) && (!ta || a.M <= (int64_t(1) << 24)) &&
          (!tb || a.N <= (int64_t(1) << 24));
 }
 
 // 256 x 256 tiles on the four-wavefront kernel where it takes the shape, else
-// on the ping-pong kernel with WAVES_M wavefront rows.
+// on the ping-pong kernel with WAVES_M wavefront rows (K % 32 == 0).
 template <int EPI, int WAVES_M = 2, bool TA = false, bool TB = false>
 static void launch_256(const GemmArgs& a, dim3 grid, hipStream_t st) {
   if (w4_takes(a, TA, TB))
@@ -1298,21 +1388,22 @@ static void launch_256(const GemmArgs& a, dim3 grid, hipStream_t st) {
     hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI, WAVES_M, 32, TA, TB>), grid, dim3(512), 0, st, a);
 }
 
-// Products with K a multiple of 32 on 256 x 256 tiles: launch_256; on 256 x
-// 128 tiles the ping-pong kernel; on 128-row tiles: the pipelined kernel; the
-// register-staged kernel (any K that is a multiple of 8) otherwise.
+// On 128-row tiles the pipelined kernel; on 256 x 256 tiles launch_256 and on
+// 256 x 128 tiles the ping-pong kernel (64-deep stages where they take the
+// shape), both only for K % 32 == 0 or K of at least 64: the register-staged
+// kernel takes the rest.
 template <int BM, int BN, int EPI>
 static void launch_epi(const GemmArgs& a, dim3 grid, hipStream_t st) {
-  if (a.K % 32 != 0) {
-    hipLaunchKernelGGL((gemm_nt_kernel<BM, BN, EPI>), grid, dim3(256), 0, st, a);
-  } else if constexpr (BM == 256 && BN == 256) {
-    launch_256<EPI>(a, grid, st);
-  } else if constexpr (BM == 256) {
-    // 64-deep stages where 256 x 128 tiles allow them (three fit in LDS)
-    if (a.K % 64 == 0) hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI, 4, 64>), grid, dim3(512), 0, st, a);
-    else hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI>), grid, dim3(512), 0, st, a);
-  } else {
+  if constexpr (BM == 128) {
     hipLaunchKernelGGL((gemm_pipe_kernel<BM, BN, EPI, 4>), grid, dim3(256), 0, st, a);
+  } else if (BN == 256 && w4_takes(a, false, false)) {
+    launch_256<EPI>(a, grid, st);
+  } else if (BN == 128 && deep_takes(a)) {
+    hipLaunchKernelGGL((gemm_pp_kernel<BM, 128, EPI, 4, 64>), grid, dim3(512), 0, st, a);
+  } else if (a.K % 32 == 0) {
+    hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, EPI>), grid, dim3(512), 0, st, a);
+  } else {
+    hipLaunchKernelGGL((gemm_nt_kernel<BM, BN, EPI>), grid, dim3(256), 0, st, a);
   }
 }
 
@@ -1326,7 +1417,8 @@ static hipError_t launch_bm(const GemmLaunch& q, hipStream_t st) {
   a.causal = q.causal;
   a.tiles_m = int((q.M + BM - 1) / BM);
   a.tiles_n = int((q.N + BN - 1) / BN);
-  const dim3 grid(unsigned(a.tiles_m * a.tiles_n), unsigned(q.batch > 1 ? q.batch : 1));
+  a.red_in = q.red_in; a.red_n = q.red_n; a.red_out = q.red_out;
+  const dim3 grid(unsigned(a.tiles_m * a.tiles_n + (q.red_out != nullptr)), unsigned(q.batch > 1 ? q.batch : 1));
   switch (q.epi) {
     case EPI_TARGET: launch_epi<BM, BN, EPI_TARGET>(a, grid, st); break;
     case EPI_LOSS:
@@ -1467,17 +1559,10 @@ hipError_t launch_gemm(const GemmLaunch& q, hipStream_t st) {
   }
 }
 
-// Deterministic loss: fixed strided fp64 partial sums, a fixed xor butterfly
-// within each wavefront, then the four wavefront totals in order.
 __global__ __launch_bounds__(256) void reduce_loss_kernel(const float* __restrict__ partials, int64_t n,
                                                           float* __restrict__ loss) {
   __shared__ double sm[4];
-  double acc = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) acc += double(partials[i]);
-  for (int msk = 32; msk >= 1; msk >>= 1) acc += __shfl_xor(acc, msk, 64);
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) loss[0] = float((sm[0] + sm[1]) + (sm[2] + sm[3]));
+  reduce_loss(partials, n, loss, sm);
 }
 
 hipError_t launch_reduce_loss(const float* partials, int64_t n, float* loss, hipStream_t st) {

@@ -174,6 +174,9 @@ struct GemmLaunch {
   HeadsParams heads;   // EPI_HEADS*
   SwigluParams swiglu; // EPI_SWIGLU
   const float* Rres;   // EPI_LOSS_BLOCK
+  // EPI_GRAD_* without batch, ta, tb: also add up red_n loss partials into
+  // *red_out (as launch_reduce_loss does), or null
+  const float* red_in; int64_t red_n; float* red_out;
 };
 
 // Causal attention with the score tiles on chip (attn_fused.hip), d = 128.

@@ -1,8 +1,10 @@
 """The 256 x 256 tile product (K a multiple of 64) at the edges of its range:
 one, two, three and five 64-deep stages, ragged rows and columns, every operand
 layout.  Against an fp64 product, and bit for bit against the same product with
-32 zero columns appended to K, which runs on the ping-pong kernel (the added
-terms are exact zeros, the order over k is the same)."""
+32 zero columns appended to K, which runs with a short first stage (the added
+terms are exact zeros, the order over k is the same).  Then K that is no multiple
+of the stages' depth, on every tile, and the loss added up beside the weight
+gradient."""
 import numpy as np
 import pytest
 import torch
@@ -59,3 +61,60 @@ def test_odd_rows(M):
     assert np.all(got[M:] == 7.0)
     mag = np.abs(A) @ np.abs(B).T
     assert np.all(np.abs(got[:M] - A.astype(np.float64) @ B.astype(np.float64).T) <= (K + 1) * 2.0 ** -24 * mag)
+
+
+# short first stages: 128 x 128, 256 x 128 and 256 x 256 tiles, one to five
+# stages, K from one chunk on (below 64 the register-staged kernel takes the
+# 256-row tiles)
+@pytest.mark.parametrize("M,N", [(301, 264), (4098, 2056), (4104, 3848)])
+@pytest.mark.parametrize("K", [8, 24, 32, 40, 56, 72, 96, 120, 136, 264])
+def test_any_k(M, N, K):
+    rs = np.random.default_rng(M + K)
+    A, B = (O.bf16_rne(rs.standard_normal((n, K)).astype(F32)) for n in (M, N))
+    out = torch.full((M, N), float("nan"), device="cuda")
+    uq.uniquan_gemm_nt(M, N, K, dev(A), dev(B), out)
+    torch.cuda.synchronize()
+    mag = np.abs(A) @ np.abs(B).T
+    err = np.abs(out.cpu().numpy() - A.astype(np.float64) @ B.astype(np.float64).T)
+    assert np.all(err <= (K + 1) * 2.0 ** -24 * mag + 1e-30)
+
+
+@pytest.mark.parametrize("a_kslow,b_kslow", [(1, 1), (0, 1), (1, 0)])
+@pytest.mark.parametrize("K", [32, 96, 160])
+def test_kslow_half_stage(K, a_kslow, b_kslow):
+    M, N = 4104, 3848
+    rs = np.random.default_rng(K + 10 * a_kslow + b_kslow)
+    A, B = (O.bf16_rne(rs.standard_normal((n, K)).astype(F32)) for n in (M, N))
+    out = torch.full((M, N), float("nan"), device="cuda")
+    uq.uniquan_gemm(M, N, K, dev(A.T if a_kslow else A), a_kslow, dev(B.T if b_kslow else B), b_kslow, out, 1.0)
+    torch.cuda.synchronize()
+    mag = np.abs(A) @ np.abs(B).T
+    err = np.abs(out.cpu().numpy() - A.astype(np.float64) @ B.astype(np.float64).T)
+    assert np.all(err <= (K + 1) * 2.0 ** -24 * mag + 1e-30)
+
+
+# weight gradients on 128 x 128, 256 x 128 and 256 x 256 tiles, from the three kernels
+@pytest.mark.parametrize("T,R,C", [(72, 130, 264), (8, 4096, 2056), (136, 4096, 2056), (104, 4096, 4096)])
+@pytest.mark.parametrize("gdt", [torch.bfloat16, torch.float32])
+def test_loss_beside_the_gradient(T, R, C, gdt):
+    """The loss is the same bits whether its own launch or the gradient's extra workgroup adds it up, and the
+    gradient the same as without it (its output over the partials takes the separate launch)."""
+    rs = np.random.default_rng(T + C)
+    X, Wh = (dev(rs.standard_normal((n, C))) for n in (T, R))
+    Yt = torch.from_numpy(rs.standard_normal((R, T)).astype(F32)).cuda()
+    n = uq.uniquan_recon_ws(T, R, C)
+    ws = torch.empty(n, device="cuda")
+    loss, loss1, loss2 = (torch.full((1,), float("nan"), device="cuda") for _ in range(3))
+    Et = torch.empty(R, T, device="cuda", dtype=torch.bfloat16)
+    G, G1 = (torch.full((R, C), float("nan"), device="cuda", dtype=gdt) for _ in range(2))
+    Xt = X.T.contiguous()
+    uq.uniquan_layer_recon(T, R, C, X, None, Wh, Yt, loss, Et, ws, None)
+    uq.uniquan_layer_grad(T, R, C, Et, Xt, G)
+    uq.uniquan_layer_recon(T, R, C, X, Xt, Wh, Yt, loss1, Et, ws, G1)
+    torch.cuda.synchronize()
+    assert loss.item() == loss1.item() and torch.equal(G, G1)
+    G1.fill_(0.0)
+    over = G1.reshape(-1).view(torch.float32)[:n]  # partials inside the gradient's output
+    uq.uniquan_layer_recon(T, R, C, X, Xt, Wh, Yt, loss2, Et, over, G1)
+    torch.cuda.synchronize()
+    assert loss.item() == loss2.item() and torch.equal(G, G1)
