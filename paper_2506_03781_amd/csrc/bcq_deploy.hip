@@ -40,17 +40,49 @@ __device__ __forceinline__ uint32_t gather_bit(uint32_t v, int i) {
   return ((t * 0x00204081u) >> 21) & 0xFu;
 }
 
-// One thread per (quad q, row r, word m): 32 code bytes -> one word per plane.
-__global__ __launch_bounds__(256) void bcq_pack_planes_kernel(const uint8_t* __restrict__ codes,
-                                                              uint32_t* __restrict__ planes, int64_t R, int64_t C,
-                                                              int k) {
+// Blocks from nb2 on: one thread per (quad q, row r, word m), 32 code bytes ->
+// one word per plane.  The others: alpha*, z*_B -> binary16, tiles of 64 rows x 16
+// group columns turned in LDS so that reads run along a row's groups and writes
+// along the rows (11008 x 4096, k = 3, g = 128: 13 us as a kernel of its own
+// with a thread per parameter, whose reads were a row apart, after 12 for the planes; 17 together here).
+__global__ __launch_bounds__(256) void bcq_pack_kernel(const uint8_t* __restrict__ codes,
+                                                       uint32_t* __restrict__ planes,
+                                                       const float* __restrict__ alpha_star,
+                                                       const float* __restrict__ z_star,
+                                                       uint16_t* __restrict__ alpha16, uint16_t* __restrict__ z16,
+                                                       int64_t R, int64_t C, int64_t gpr, int k, unsigned nb2) {
+  constexpr int TR = 64, TJ = 16;
+  __shared__ uint16_t t[5][TJ][TR + 2];  // k <= 4 scales and the offset
+  if (blockIdx.x < nb2) {
+    const uint32_t nj = uint32_t((gpr + TJ - 1) / TJ), rt = blockIdx.x / nj;
+    const int64_t r0 = int64_t(rt) * TR, j0 = int64_t(blockIdx.x - rt * nj) * TJ;
+    const int nr = int(min<int64_t>(TR, R - r0)), ng = int(min<int64_t>(TJ, gpr - j0));
+    auto half = [](float v) { return __builtin_bit_cast(uint16_t, _Float16(v)); };
+    const uint32_t per = ng * k;
+    for (uint32_t e = threadIdx.x; e < nr * per; e += 256) {
+      const uint32_t r = e / per, c = e - r * per, j = c / uint32_t(k);
+      t[c - j * k][j][r] = half(alpha_star[((r0 + r) * gpr + j0) * k + c]);
+    }
+    for (int e = threadIdx.x; e < nr * ng; e += 256) {
+      const int r = e / ng, j = e - r * ng;
+      t[k][j][r] = half(z_star[(r0 + r) * gpr + j0 + j]);
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < (k + 1) * ng * TR; e += 256) {
+      const int r = e & (TR - 1), c = e / TR, i = c / ng, j = c - i * ng;
+      if (r >= nr) continue;
+      uint16_t* out = i < k ? alpha16 + int64_t(i) * gpr * R : z16;
+      out[(j0 + j) * R + r0 + r] = t[i][j][r];
+    }
+    return;
+  }
   const int64_t nq = C / 128;
-  const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const uint32_t idx = (blockIdx.x - nb2) * 256 + threadIdx.x;  // below 2^32: a launch has no more threads
   if (idx >= nq * R * 4) return;
-  const int m = int(idx & 3);
-  const int64_t rq = idx >> 2;  // q R + r
-  const int64_t q = rq / R, r = rq - q * R;
-  const uint4* src = reinterpret_cast<const uint4*>(codes + r * C + q * 128 + m * 32);
+  const uint32_t m = idx & 3, rq = idx >> 2;  // q R + r
+  const uint32_t q = rq / uint32_t(R);
+  const int64_t r = rq - q * uint32_t(R);
+  const uint4* src = reinterpret_cast<const uint4*>(codes + r * C + int64_t(q) * 128 + m * 32);
   const uint4 lo = src[0], hi = src[1];
   const uint32_t v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
   for (int i = 0; i < k; ++i) {
@@ -61,28 +93,19 @@ __global__ __launch_bounds__(256) void bcq_pack_planes_kernel(const uint8_t* __r
   }
 }
 
-// One thread per (group column j, row r): alpha*, z*_B -> binary16.
-__global__ __launch_bounds__(256) void bcq_pack_params_kernel(const float* __restrict__ alpha_star,
-                                                              const float* __restrict__ z_star,
-                                                              uint16_t* __restrict__ alpha16,
-                                                              uint16_t* __restrict__ z16, int64_t R, int64_t gpr,
-                                                              int k) {
-  const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (idx >= gpr * R) return;
-  const int64_t j = idx / R, r = idx - j * R;
-  const int64_t gid = r * gpr + j;
-  for (int i = 0; i < k; ++i)
-    alpha16[(int64_t(i) * gpr + j) * R + r] = __builtin_bit_cast(uint16_t, _Float16(alpha_star[gid * k + i]));
-  z16[j * R + r] = __builtin_bit_cast(uint16_t, _Float16(z_star[gid]));
-}
-
 hipError_t launch_bcq_pack(const BcqPackLaunch& p, hipStream_t st) {
   const int64_t nq = p.C / 128, gpr = p.C / p.g;
-  const int64_t n1 = nq * p.R * 4, n2 = gpr * p.R;
-  hipLaunchKernelGGL(bcq_pack_planes_kernel, dim3(unsigned((n1 + 255) / 256)), dim3(256), 0, st, p.codes, p.planes,
-                     p.R, p.C, p.k);
-  hipLaunchKernelGGL(bcq_pack_params_kernel, dim3(unsigned((n2 + 255) / 256)), dim3(256), 0, st, p.alpha_star,
-                     p.z_star, p.alpha16, p.z16, p.R, gpr, p.k);
+  const int64_t nb1 = (nq * p.R * 4 + 255) / 256, nb2 = ((p.R + 63) / 64) * ((gpr + 15) / 16);
+  auto launch = [&](int64_t planes, int64_t params) {
+    hipLaunchKernelGGL(bcq_pack_kernel, dim3(unsigned(planes + params)), dim3(256), 0, st, p.codes, p.planes,
+                       p.alpha_star, p.z_star, p.alpha16, p.z16, p.R, p.C, gpr, p.k, unsigned(params));
+  };
+  if (nb1 + nb2 < (int64_t(1) << 24)) {
+    launch(nb1, nb2);
+  } else {  // a launch takes fewer than 2^32 threads
+    launch(nb1, 0);
+    launch(0, nb2);
+  }
   return hipGetLastError();
 }
 

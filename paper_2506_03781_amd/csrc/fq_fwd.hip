@@ -95,13 +95,6 @@ struct FwdArgs {
   int resid;  // 1: store What - W (the reconstruction residual) instead of What
 };
 
-// Dynamic LDS of a quantizer tile: the level tables plus four per-group
-// fp32 arrays.
-static size_t tile_lds_bytes(const TileGeom& t) {
-  const size_t e = size_t(t.tile_groups) << t.logL;
-  return ((e * 10 + 15) & ~size_t(15)) + 16 * size_t(t.tile_groups);
-}
-
 // Per-wave LDS bytes: the level tables of (512 ch / g) groups of 2^k levels,
 // optionally the local-mapping neighbour table (16 B per level), and 4
 // floats per group.
@@ -533,73 +526,135 @@ struct FoldArgs {
   int code_src;
 };
 
-// LDS: tables, per-group (Delta s_r, z_U, z*) and the tile's alpha* (k per group)
-static size_t fold_lds_bytes(const TileGeom& t) {
-  return tile_lds_bytes(t) + 4 * size_t(t.tile_groups) * size_t(t.k);
-}
-
-template <int WDT>
+// Each wavefront owns 512 consecutive weights with their groups' tables in its
+// own LDS, as the forward does.  Up to 8 levels the nearest one is found by
+// trying all of them from registers (a lane's 8 weights lie in one group), which
+// is the definition of the mapping, first of the smallest |fl(x - q_j)|, in four
+// instructions a level without the dependent LDS reads of a search; from 16
+// levels on the search is shorter.
+// 11008 x 4096, k = 3, g = 128: 75 us against 106 with workgroup-wide tables,
+// k and the levels as variables and the search (the 7 bytes a weight take 60 us).
+template <int WDT, int LOGL>
 __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int L = 1 << LOGL, K = LOGL;
+  constexpr bool scan = LOGL <= 3;
   const TileGeom& g = a.t;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int gw = 512 >> g.logg;  // groups per wave
   LevelTables tab;
-  float* s_ds = reinterpret_cast<float*>(carve_tables(tab, smem, g.tile_groups << g.logL));
-  float* s_zu = s_ds + g.tile_groups;
-  float* s_zst = s_zu + g.tile_groups;
-  float* s_alpha = s_zst + 2 * g.tile_groups;  // tile_groups * k entries
-  const int64_t Gn = g.N >> g.logg;
-  const int64_t gid0 = int64_t(blockIdx.x) * g.tile_groups;
-  const int ng = int(min<int64_t>(g.tile_groups, Gn - gid0));
-  const int lane_w = threadIdx.x * kVec;
-  const int64_t off = (gid0 << g.logg) + lane_w;
+  float* s_ds = reinterpret_cast<float*>(carve_tables(tab, smem + size_t(wave) * wave_lds_bytes(g.logg, LOGL, false),
+                                                      gw << LOGL));
+  float* s_zu = s_ds + gw;
+  uint32_t* s_codes = reinterpret_cast<uint32_t*>(s_zu + gw);  // the sorted levels' codes, 4 bits each (scan)
+  const int64_t wbase = (int64_t(blockIdx.x) * (blockDim.x >> 6) + wave) * 512;  // first weight of this wave
+  if (wbase >= g.N) return;                                                      // whole wave past the end
+  const int gv = int(min<int64_t>(512, g.N - wbase)) >> g.logg;                  // valid groups
+  const int ev = gv << LOGL;
+  const int64_t gid0 = wbase >> g.logg;
 
-  for (int gl = threadIdx.x; gl < ng; gl += blockDim.x) {
+  // The parameters of the first 64 groups and levels are loaded first and the
+  // weights right behind them, so that the tables are built while the weights
+  // arrive (loads complete in order); lanes past the end repeat the last.
+  struct Group {
+    float dl, zu, sr, zb, al[K];
+  };
+  auto load_group = [&](int64_t gid, bool row_scale) {
+    Group p;
+    p.dl = a.delta ? a.delta[gid] : 1.0f;
+    p.zu = a.z_u ? a.z_u[gid] : 0.0f;
+    p.sr = row_scale && a.s_r ? a.s_r[uint32_t(gid) / uint32_t(g.gpr)] : 1.0f;
+    p.zb = a.z_b[gid];
+#pragma unroll
+    for (int i = 0; i < K; ++i) p.al[i] = a.alpha[gid * K + i];
+    return p;
+  };
+  const Group pg = load_group(gid0 + min(lane, gv - 1), true);
+  const Group pe = load_group(gid0 + (min(lane, ev - 1) >> LOGL), false);
+  const int64_t off = wbase + min(lane * kVec, (gv << g.logg) - kVec);
+  Raw8<WDT> w;
+  float sv[8];
+  if (a.codes != nullptr) {
+    w.load(a.W, off);
+    if (a.code_src == 0) load8f(a.s, off, sv);
+  }
+  auto put_group = [&](int gl, const Group& p) {
     const int64_t gid = gid0 + gl;
-    const float dl = a.delta ? a.delta[gid] : 1.0f;
-    const float zu = a.z_u ? a.z_u[gid] : 0.0f;
-    const float sr = a.s_r ? a.s_r[uint32_t(gid) / uint32_t(g.gpr)] : 1.0f;
-    const float zst = dl * (a.z_b[gid] - zu);
-    for (int i = 0; i < g.k; ++i) {
-      const float as = dl * a.alpha[gid * g.k + i];
-      a.alpha_star[gid * g.k + i] = as;
-      s_alpha[gl * g.k + i] = as;
-    }
-    a.z_star[gid] = zst;
-    s_zst[gl] = zst;
-    s_ds[gl] = dl * sr;
-    s_zu[gl] = zu;
-  }
+#pragma unroll
+    for (int i = 0; i < K; ++i) a.alpha_star[gid * K + i] = p.dl * p.al[i];
+    a.z_star[gid] = p.dl * (p.zb - p.zu);
+    s_ds[gl] = p.dl * p.sr;
+    s_zu[gl] = p.zu;
+  };
+  auto put_level = [&](int e, const Group& p) {
+    float al[K], zb = p.zb;
+#pragma unroll
+    for (int i = 0; i < K; ++i) al[i] = a.code_src == 0 ? p.al[i] : p.dl * p.al[i];  // 1: the folded levels
+    if (a.code_src != 0) zb = p.dl * (zb - p.zu);
+    tab.raw[e] = level_value_k<LOGL>(al, zb, e & (L - 1));
+  };
+  if (lane < ev) put_level(lane, pe);
+  if (lane < gv) put_group(lane, pg);
+  for (int gl = lane + 64; gl < gv; gl += 64) put_group(gl, load_group(gid0 + gl, true));
   if (a.codes == nullptr) return;  // uniform across the grid
-  __syncthreads();
-  if (a.code_src == 0) {
-    build_tables(tab, a.alpha, a.z_b, gid0, ng, g.k, g.logL);
-  } else {
-    const int L = 1 << g.logL;
-    for (int e = threadIdx.x; e < (ng << g.logL); e += blockDim.x) {
-      const int gl = e >> g.logL;
-      tab.raw[e] = level_value(s_alpha + gl * g.k, s_zst[gl], g.k, e & (L - 1));
+  for (int e = lane + 64; e < ev; e += 64) put_level(e, load_group(gid0 + (e >> LOGL), false));
+  wave_lds_sync();
+  for (int e = lane; e < ev; e += 64) {
+    const int b = e & (L - 1), base = e - b;
+    const float q = tab.raw[e];
+    int rank = 0;
+#pragma unroll
+    for (int b2 = 0; b2 < L; ++b2) {
+      const float q2 = tab.raw[base + b2];
+      rank += (q2 < q) | ((q2 == q) & (b2 < b));
     }
-    __syncthreads();
-    sort_tables(tab, ng, g.logL);
+    tab.qs[base + rank] = q;
+    tab.code_of[base + rank] = uint8_t(b);
   }
-  if (lane_w >= (ng << g.logg)) return;
-  const int glw = lane_w >> g.logg;
-  float w[8], sv[8];
-  load8<WDT>(a.W, off, w);
-  if (a.code_src == 0) load8f(a.s, off, sv);
-  const float* q = tab.qs + (glw << g.logL);
-  const uint8_t* code_of = tab.code_of + (glw << g.logL);
+  wave_lds_sync();
+  if constexpr (scan) {
+    for (int gl = lane; gl < gv; gl += 64) {
+      uint32_t c = 0;
+#pragma unroll
+      for (int j = 0; j < L; ++j) c |= uint32_t(tab.code_of[(gl << LOGL) + j]) << (4 * j);
+      s_codes[gl] = c;
+    }
+    wave_lds_sync();
+  }
+  const int gl = (lane * kVec) >> g.logg;
+  if (gl >= gv) return;
+  const float ds = s_ds[gl], zu = s_zu[gl];
+  const float* q = tab.qs + (gl << LOGL);
+  const uint32_t codes = scan ? s_codes[gl] : 0;
+  float ql[scan ? L : 1];
+  if constexpr (scan) {
+#pragma unroll
+    for (int j = 0; j < L; ++j) ql[j] = q[j];
+  }
   uint32_t cw[2] = {0u, 0u};
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    float x = w[i];
+    float x = w.get(i);
     if (a.code_src == 0) {
-      const float den = s_ds[glw] * sv[i];
-      x = x / den + s_zu[glw];
+      const float den = ds * sv[i];
+      x = x / den + zu;
     }
-    float d;
-    const int j = nearest_full(q, g.logL, x, d);
-    cw[i >> 2] |= uint32_t(code_of[j]) << (8 * (i & 3));
+    uint32_t code;
+    if constexpr (scan) {
+      float bd = fabsf(x - ql[0]);
+      uint32_t sh = 0;
+#pragma unroll
+      for (int j = 1; j < L; ++j) {
+        const float dj = fabsf(x - ql[j]);
+        sh = dj < bd ? 4u * j : sh;
+        bd = dj < bd ? dj : bd;
+      }
+      code = (codes >> sh) & uint32_t(L - 1);
+    } else {
+      float d;
+      code = tab.code_of[(gl << LOGL) + nearest_full_k<LOGL>(q, x, d)];
+    }
+    cw[i >> 2] |= code << (8 * (i & 3));
   }
   store8u8(a.codes, off, make_uint2(cw[0], cw[1]));
 }
@@ -1337,6 +1392,35 @@ hipError_t launch_fq_step(const FqStepLaunch& p, hipStream_t st) {
   return launch_fq_fwd(f, st);
 }
 
+template <int WD, int LOGL>
+static hipError_t launch_fold_l(const FoldArgs& a, hipStream_t st) {
+  auto kern = fold_kernel<WD, LOGL>;
+  const size_t wave_bytes = wave_lds_bytes(a.t.logg, LOGL, false);
+  const int wpb = fwd_waves_per_block(wave_bytes);
+  const size_t lds = size_t(wpb) * wave_bytes;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+  }
+  const int64_t waves = (a.t.N + 511) / 512;
+  hipLaunchKernelGGL(kern, dim3(unsigned((waves + wpb - 1) / wpb)), dim3(64 * wpb), lds, st, a);
+  return hipGetLastError();
+}
+
+template <int WD>
+static hipError_t launch_fold_k(const FoldArgs& a, hipStream_t st) {
+  switch (a.t.k) {
+    case 1: return launch_fold_l<WD, 1>(a, st);
+    case 2: return launch_fold_l<WD, 2>(a, st);
+    case 3: return launch_fold_l<WD, 3>(a, st);
+    case 4: return launch_fold_l<WD, 4>(a, st);
+    case 5: return launch_fold_l<WD, 5>(a, st);
+    case 6: return launch_fold_l<WD, 6>(a, st);
+    default: return launch_fold_l<WD, 7>(a, st);
+  }
+}
+
 hipError_t launch_fold(const FoldLaunch& p, hipStream_t st) {
   if (p.g > 512) {
     BigArgs b = big_args(p.R, p.C, p.k, p.g);
@@ -1350,11 +1434,7 @@ hipError_t launch_fold(const FoldLaunch& p, hipStream_t st) {
   a.W = p.W; a.s = p.s; a.s_r = p.s_r; a.delta = p.delta; a.z_u = p.z_u;
   a.alpha = p.alpha; a.z_b = p.z_b; a.alpha_star = p.alpha_star; a.z_star = p.z_star;
   a.codes = p.codes; a.code_src = p.code_src;
-  const dim3 grid(grid_of(a.t)), block(kThreads);
-  const size_t lds = fold_lds_bytes(a.t);
-  if (p.w_dtype == BF16) hipLaunchKernelGGL((fold_kernel<BF16>), grid, block, lds, st, a);
-  else hipLaunchKernelGGL((fold_kernel<F32>), grid, block, lds, st, a);
-  return hipGetLastError();
+  return p.w_dtype == BF16 ? launch_fold_k<BF16>(a, st) : launch_fold_k<F32>(a, st);
 }
 
 hipError_t launch_dequant(const DequantLaunch& p, hipStream_t st) {

@@ -112,46 +112,6 @@ __device__ __forceinline__ char* carve_tables(LevelTables& t, char* p, int entri
   return p + ((size_t(entries) * 10 + 15) & ~size_t(15));
 }
 
-// Rank every raw level of the tile's groups (sort key (value, code)) and
-// scatter into the sorted arrays.  Callers have filled t.raw and issued a
-// barrier; ends with a barrier.
-__device__ __forceinline__ void sort_tables(LevelTables& t, int ng, int logL) {
-  const int L = 1 << logL;
-  const int n = ng << logL;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {
-    const int gl = e >> logL;
-    const int b = e & (L - 1);
-    const float* row = t.raw + (gl << logL);
-    const float q = row[b];
-    int rank = 0;
-    for (int b2 = 0; b2 < L; ++b2) {
-      const float q2 = row[b2];
-      rank += (q2 < q) | ((q2 == q) & (b2 < b));
-    }
-    t.qs[(gl << logL) + rank] = q;
-    t.code_of[(gl << logL) + rank] = uint8_t(b);
-    t.pos_of[(gl << logL) + b] = uint8_t(rank);
-  }
-  __syncthreads();
-}
-
-// Build the sorted tables of groups gid0 .. gid0+ng-1 from alpha and z_b.
-// All threads of the block take part; ends with a block barrier.
-__device__ __forceinline__ void build_tables(LevelTables& t, const float* __restrict__ alpha,
-                                             const float* __restrict__ z_b, int64_t gid0, int ng,
-                                             int k, int logL) {
-  const int L = 1 << logL;
-  const int n = ng << logL;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {
-    const int gl = e >> logL;
-    const int b = e & (L - 1);
-    const int64_t gid = gid0 + gl;
-    t.raw[e] = level_value(alpha + gid * k, z_b[gid], k, b);
-  }
-  __syncthreads();
-  sort_tables(t, ng, logL);
-}
-
 // Nearest sorted level of x among q[0..L-1] (ascending).  Returns the first
 // position with the smallest |fl(x - q_j)|, i.e. the lower level on ties.
 // Since rounding is monotone, |fl(x - q_j)| is non-increasing up to the last
@@ -159,10 +119,12 @@ __device__ __forceinline__ void build_tables(LevelTables& t, const float* __rest
 // {a, b} found by binary search; a run of equal distances ending at a is
 // walked back to its first element (duplicate levels, or levels closer than
 // the distance's ulp).
-__device__ __forceinline__ int nearest_full(const float* __restrict__ q, int logL, float x, float& dist) {
+template <int LOGL>
+__device__ __forceinline__ int nearest_full_k(const float* __restrict__ q, float x, float& dist) {
+  constexpr int L = 1 << LOGL;
   int pos = 0;  // number of levels <= x among q[0 .. L-2]
-  for (int step = (1 << logL) >> 1; step >= 1; step >>= 1)
-    pos += (q[pos + step - 1] <= x) ? step : 0;
+#pragma unroll
+  for (int step = L >> 1; step >= 1; step >>= 1) pos += (q[pos + step - 1] <= x) ? step : 0;
   const int a = pos > 0 ? pos - 1 : 0;
   const int b = pos;
   const float da = fabsf(x - q[a]);
@@ -172,7 +134,7 @@ __device__ __forceinline__ int nearest_full(const float* __restrict__ q, int log
     return b;
   }
   int j = a;
-  if (a > 0 && fabsf(x - q[a - 1]) == da) {
+  if (a > 0 && fabsf(x - q[a - 1]) == da) {  // run of equal distances: take its first element
     j = 0;
     while (j < a && fabsf(x - q[j]) != da) ++j;
   }
@@ -200,30 +162,6 @@ __device__ __forceinline__ int nearest_local(const float* __restrict__ q, int L,
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
   __builtin_amdgcn_wave_barrier();
-}
-
-// nearest_full with the table size fixed at compile time (unrolled search).
-template <int LOGL>
-__device__ __forceinline__ int nearest_full_k(const float* __restrict__ q, float x, float& dist) {
-  constexpr int L = 1 << LOGL;
-  int pos = 0;  // number of levels <= x among q[0 .. L-2]
-#pragma unroll
-  for (int step = L >> 1; step >= 1; step >>= 1) pos += (q[pos + step - 1] <= x) ? step : 0;
-  const int a = pos > 0 ? pos - 1 : 0;
-  const int b = pos;
-  const float da = fabsf(x - q[a]);
-  const float db = fabsf(x - q[b]);
-  if (db < da) {
-    dist = db;
-    return b;
-  }
-  int j = a;
-  if (a > 0 && fabsf(x - q[a - 1]) == da) {  // run of equal distances: take its first element
-    j = 0;
-    while (j < a && fabsf(x - q[j]) != da) ++j;
-  }
-  dist = da;
-  return j;
 }
 
 }  // namespace uq

@@ -178,3 +178,31 @@ def test_rejects_bad_shapes():
         uq.uniquan_bcq_matmul(9, 64, 128, 2, 128, torch.zeros(9 * 128, dtype=torch.bfloat16, device=DEV),
                               t, h, h, torch.zeros(9 * 64, device=DEV))
     assert e.value.status == uq.UQ_EUNSUPPORTED
+
+
+# the fold's table forms: 64 groups a wavefront, levels by the scan (k <= 3) and
+# by the search, a ragged last wavefront; equal levels and weights half-way
+# between levels (the lower level, the smaller code), zero scales of a level
+@pytest.mark.parametrize("R,C,k,g", [(3, 264, 3, 8), (5, 264, 7, 8), (2, 1040, 4, 16), (7, 640, 2, 128),
+                                     (1, 512, 1, 512), (9, 384, 3, 64)])
+@pytest.mark.parametrize("code_src", [0, 1])
+def test_fold_edges(R, C, k, g, code_src):
+    rs = np.random.default_rng(R + C + k)
+    Gn = R * C // g
+    W = (rs.integers(-40, 41, (R, C)) / 8.0).astype(np.float32)  # bf16-exact, on levels and midpoints
+    s = np.where(rs.random((R, C)) < 0.5, 1.0, rs.uniform(0.9, 1.1, (R, C))).astype(np.float32)
+    alpha = (rs.integers(0, 5, (Gn, k)) / 4.0).astype(np.float32)
+    delta = rs.choice([0.5, 1.0, 0.3], Gn).astype(np.float32)
+    z_u, z_b = (rs.integers(-4, 5, Gn) / 2.0 for _ in range(2))
+    z_u, z_b = z_u.astype(np.float32), z_b.astype(np.float32)
+    fo = U.fold(W, s, alpha, z_b, k, g, None, delta, z_u, code_src)
+    for dt in (torch.bfloat16, torch.float32):
+        a_st, z_st = torch.empty(Gn * k, device=DEV), torch.empty(Gn, device=DEV)
+        cd = torch.empty(R * C, dtype=torch.uint8, device=DEV)
+        uq.uniquan_fold_to_bcq(R, C, k, g, dev(W, dt), dev(s, torch.float32), None, dev(delta, torch.float32),
+                               dev(z_u, torch.float32), dev(alpha.reshape(-1), torch.float32), dev(z_b, torch.float32),
+                               a_st, z_st, cd, code_src)
+        torch.cuda.synchronize()
+        assert np.array_equal(cd.cpu().numpy().reshape(R, C), fo["codes"])
+        assert np.array_equal(a_st.cpu().numpy(), fo["alpha_star"].reshape(-1))
+        assert np.array_equal(z_st.cpu().numpy(), fo["z_star"].reshape(-1))
