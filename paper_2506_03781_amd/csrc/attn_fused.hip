@@ -274,20 +274,58 @@ __device__ __forceinline__ void copy_tile(const uint16_t* base, const uint32_t (
   for (int q = 0; q < PW; ++q) copy16(base, off[q], tile + (wave * PW + q) * 64);
 }
 
+// Split walks (KS = 2): a workgroup has KS groups of NW waves that own the same
+// rows and take every KS-th tile of the walk, each with its own stages.  A wave
+// handles a tile in a chain of dependent products and exponentials of ~1500
+// cycles; where the rows give about one wave per SIMD nothing hides it, and two
+// groups halve the walk (16 heads of 1056 x 2 sequences: forward 45 -> 35 us,
+// queries 42 -> 38, keys and values 64 -> 52).  At more waves per SIMD the split
+// only adds the exchange.
+//
+// Sum of a 128 x 32 fp32 accumulator over the two groups, in the first group's
+// registers: the second group's goes through LDS (NW * 16 KB of smem; all waves
+// call it, past a barrier that follows the last read of the stages).
+template <int NW>
+__device__ __forceinline__ void add_groups(f32x16a (&acc)[4], float* smem, int wave, int ks, int lane) {
+  float* mine = smem + wave * 4096 + lane * 4;
+  if (ks == 1) {
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; r += 4)
+        *reinterpret_cast<float4*>(mine + (4 * db + r / 4) * 256) =
+            make_float4(acc[db][r], acc[db][r + 1], acc[db][r + 2], acc[db][r + 3]);
+  }
+  lds_wait_barrier();
+  if (ks == 0) {
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; r += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(mine + (4 * db + r / 4) * 256);
+        acc[db][r] += v.x;
+        acc[db][r + 1] += v.y;
+        acc[db][r + 2] += v.z;
+        acc[db][r + 3] += v.w;
+      }
+  }
+}
+
 // Forward: one workgroup of NW waves per (NW * 32 queries, query batch); wave
 // w owns 32 queries and multiplies the key tiles up to its diagonal (the
 // workgroup copies the tiles up to its last diagonal).  Key and value
 // fragments go from LDS straight into their MFMAs rather than into arrays
 // held across the tile: 156 registers, so three waves share a SIMD and one
 // wave's exponentials overlap another's products (two waves per SIMD at 243).
-template <int NW, int S, bool TOK>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) void attn_fwd_kernel(AttnArgs a) {
+template <int NW, int S, bool TOK, int KS>
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(KS == 1 ? 3 : 2))) void attn_fwd_kernel(AttnArgs a) {
   constexpr int QB = NW * NB;
   constexpr int PW = 8 / NW;  // copy blocks per wave and tile
   constexpr int STAGE = 2 * TILE16;  // key tile, value tile
-  __shared__ u32x4a smem[S * STAGE];
+  __shared__ u32x4a smem[S * KS * STAGE];
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int wave = wv % NW, ks = wv / NW;
   const int L = a.L;
   int qb;
   int64_t b;
@@ -298,6 +336,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   const int qi = q0 + (lane & 31);  // this lane's query
   const int n_tiles = min(L, qb * QB + QB) / NB;
   const int my_tiles = active ? q0 / NB + 1 : 0;
+  // step i of the walk: tile i KS + ks (past the end the last tile is copied, unused)
+  const int n_steps = (n_tiles + KS - 1) / KS;
+  auto tile_at = [&](int i) { return int64_t(KS == 1 ? i : min(i * KS + ks, n_tiles - 1)); };
+  auto stage_at = [&](int i) { return smem + ((i % S) * KS + ks) * STAGE; };
   const uint16_t* Kb = a.K + bk * int64_t(L) * D;
   const uint16_t* Vb = a.V + bk * int64_t(L) * D;
   const float c = a.scale * LOG2E;
@@ -314,16 +356,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   float m = -INFINITY, l = 0.0f;
 #pragma unroll
   for (int t = 0; t < S - 1; ++t)
-    if (t < n_tiles) copy_tile<PW>(Kb + int64_t(t) * NB * D, ro, smem + (t % S) * STAGE, wave);
-  for (int t = 0; t < n_tiles; ++t) {
-    wait_tiles<PW>(min(S - 2, n_tiles - 1 - t));
+    if (t < n_steps) copy_tile<PW>(Kb + tile_at(t) * NB * D, ro, stage_at(t), wave);
+  for (int i = 0; i < n_steps; ++i) {
+    wait_tiles<PW>(min(S - 2, n_steps - 1 - i));
     lds_wait_barrier();
-    if (t + S - 1 < n_tiles) {
-      const int u = t + S - 1;
-      copy_tile<PW>(Kb + int64_t(u) * NB * D, ro, smem + (u % S) * STAGE, wave);
+    if (i + S - 1 < n_steps) {
+      const int u = i + S - 1;
+      copy_tile<PW>(Kb + tile_at(u) * NB * D, ro, stage_at(u), wave);
     }
+    const int t = i * KS + ks;
     if (t >= my_tiles) continue;
-    const u32x4a* tk = smem + (t % S) * STAGE;
+    const u32x4a* tk = stage_at(i);
     f32x16a s = zero16();
 #pragma unroll
     for (int j = 0; j < 8; ++j) s = mfma(row_frag(tk, j, lane), qf[j], s);
@@ -345,6 +388,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   }
   // the two half-waves of a query (lower half first) -> lse
   float lse;
+  lds_wait_barrier();  // every wave is past pass 1's reads before the stages are refilled
+  if constexpr (KS == 2) {
+    // maximum and sum of both groups per lane, the first group's first
+    float2* ex = reinterpret_cast<float2*>(smem) + wave * 128 + lane;
+    ex[ks * 64] = make_float2(m, l);
+    lds_wait_barrier();
+    const float2 u = ex[0], v = ex[64];
+    const float mm = fmaxf(u.x, v.x);
+    const float ms = mm == -INFINITY ? 0.0f : mm;
+    l = u.y * exp2a(u.x - ms) + v.y * exp2a(v.x - ms);
+    m = mm;
+    lds_wait_barrier();
+  }
   {
     const float m2 = __shfl_xor(m, 32, 64), l2 = __shfl_xor(l, 32, 64);
     const float mlo = (lane < 32) ? m : m2, llo = (lane < 32) ? l : l2;
@@ -354,25 +410,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
     const float lt = llo * exp2a(mlo - ms) + lhi * exp2a(mhi - ms);
     lse = mm + __builtin_amdgcn_logf(lt);  // log2
   }
-  lds_wait_barrier();  // every wave is past pass 1's reads before the stages are refilled
   // pass 2: P = bf16(2^(c S - lse)), O += P V
   f32x16a o[4] = {zero16(), zero16(), zero16(), zero16()};
 #pragma unroll
   for (int t = 0; t < S - 1; ++t)
-    if (t < n_tiles) {
-      copy_tile<PW>(Kb + int64_t(t) * NB * D, ro, smem + (t % S) * STAGE, wave);
-      copy_tile<PW>(Vb + int64_t(t) * NB * D, ro, smem + (t % S) * STAGE + TILE16, wave);
+    if (t < n_steps) {
+      copy_tile<PW>(Kb + tile_at(t) * NB * D, ro, stage_at(t), wave);
+      copy_tile<PW>(Vb + tile_at(t) * NB * D, ro, stage_at(t) + TILE16, wave);
     }
-  for (int t = 0; t < n_tiles; ++t) {
-    wait_tiles<2 * PW>(min(S - 2, n_tiles - 1 - t));
+  for (int i = 0; i < n_steps; ++i) {
+    wait_tiles<2 * PW>(min(S - 2, n_steps - 1 - i));
     lds_wait_barrier();
-    if (t + S - 1 < n_tiles) {
-      const int u = t + S - 1;
-      copy_tile<PW>(Kb + int64_t(u) * NB * D, ro, smem + (u % S) * STAGE, wave);
-      copy_tile<PW>(Vb + int64_t(u) * NB * D, ro, smem + (u % S) * STAGE + TILE16, wave);
+    if (i + S - 1 < n_steps) {
+      const int u = i + S - 1;
+      copy_tile<PW>(Kb + tile_at(u) * NB * D, ro, stage_at(u), wave);
+      copy_tile<PW>(Vb + tile_at(u) * NB * D, ro, stage_at(u) + TILE16, wave);
     }
+    const int t = i * KS + ks;
     if (t >= my_tiles) continue;
-    const u32x4a* tk = smem + (t % S) * STAGE;
+    const u32x4a* tk = stage_at(i);
     const u32x4a* tv = tk + TILE16;
     f32x16a s = zero16();
 #pragma unroll
@@ -391,6 +447,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
 #pragma unroll
       for (int db = 0; db < 4; ++db) o[db] = mfma(col_frag(tv, db, h, lane), pb, o[db]);
     }
+  }
+  if constexpr (KS == 2) {
+    lds_wait_barrier();
+    add_groups<NW>(o, reinterpret_cast<float*>(smem), wave, ks, lane);
+    if (ks != 0) return;
   }
   if (!active) return;
   uint16_t* orow = a.O_out + (TOK ? tok_off(a, b, qi) : (b * L + qi) * int64_t(D));
@@ -415,14 +476,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
 // Backward for the queries: delta = dO . O per row, then per key tile
 // S -> P (from lse), dP = dO V^T, dS = bf16(P (dP - delta)), dQ += dS K;
 // dQ * scale stored in fp32, delta stored for the key kernel.
-template <int NW, int S, bool TOK>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_kernel(AttnArgs a) {
+template <int NW, int S, bool TOK, int KS>
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_kernel(AttnArgs a) {
   constexpr int QB = NW * NB;
   constexpr int PW = 8 / NW;
   constexpr int STAGE = 2 * TILE16;  // key tile, value tile
-  __shared__ u32x4a smem[S * STAGE];
+  __shared__ u32x4a smem[S * KS * STAGE];
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int wave = wv % NW, ks = wv / NW;
   const int L = a.L;
   int qb;
   int64_t b;
@@ -434,6 +496,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int qc = min(qi, L - 1);
   const int n_tiles = min(L, qb * QB + QB) / NB;
   const int my_tiles = active ? q0 / NB + 1 : 0;
+  // step i of the walk, as in the forward
+  const int n_steps = (n_tiles + KS - 1) / KS;
+  auto tile_at = [&](int i) { return int64_t(KS == 1 ? i : min(i * KS + ks, n_tiles - 1)); };
+  auto stage_at = [&](int i) { return smem + ((i % S) * KS + ks) * STAGE; };
   const uint16_t* Kb = a.K + bk * int64_t(L) * D;
   const uint16_t* Vb = a.V + bk * int64_t(L) * D;
   const float c = a.scale * LOG2E;
@@ -462,22 +528,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   f32x16a dq[4] = {zero16(), zero16(), zero16(), zero16()};
 #pragma unroll
   for (int t = 0; t < S - 1; ++t)
-    if (t < n_tiles) {
-      u32x4a* st = smem + (t % S) * STAGE;
-      copy_tile<PW>(Kb + int64_t(t) * NB * D, ro, st, wave);
-      copy_tile<PW>(Vb + int64_t(t) * NB * D, ro, st + TILE16, wave);
+    if (t < n_steps) {
+      copy_tile<PW>(Kb + tile_at(t) * NB * D, ro, stage_at(t), wave);
+      copy_tile<PW>(Vb + tile_at(t) * NB * D, ro, stage_at(t) + TILE16, wave);
     }
-  for (int t = 0; t < n_tiles; ++t) {
-    wait_tiles<2 * PW>(min(S - 2, n_tiles - 1 - t));
+  for (int it = 0; it < n_steps; ++it) {
+    wait_tiles<2 * PW>(min(S - 2, n_steps - 1 - it));
     lds_wait_barrier();
-    if (t + S - 1 < n_tiles) {
-      const int u = t + S - 1;
-      u32x4a* st = smem + (u % S) * STAGE;
-      copy_tile<PW>(Kb + int64_t(u) * NB * D, ro, st, wave);
-      copy_tile<PW>(Vb + int64_t(u) * NB * D, ro, st + TILE16, wave);
+    if (it + S - 1 < n_steps) {
+      const int u = it + S - 1;
+      copy_tile<PW>(Kb + tile_at(u) * NB * D, ro, stage_at(u), wave);
+      copy_tile<PW>(Vb + tile_at(u) * NB * D, ro, stage_at(u) + TILE16, wave);
     }
+    const int t = it * KS + ks;
     if (t >= my_tiles) continue;
-    const u32x4a* tk = smem + (t % S) * STAGE;
+    const u32x4a* tk = stage_at(it);
     bf16x8a f[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) f[j] = row_frag(tk, j, lane);
@@ -507,6 +572,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       for (int db = 0; db < 4; ++db) dq[db] = mfma(f[4 * h + db], sb, dq[db]);
     }
   }
+  if constexpr (KS == 2) {
+    lds_wait_barrier();
+    add_groups<NW>(dq, reinterpret_cast<float*>(smem), wave, ks, lane);
+    if (ks != 0) return;
+  }
   if (!active) return;
   if (lane < 32) a.delta[b * L + qi] = dl;
   if constexpr (TOK) store_bf16_row<true>(a.dQ_tok + tok_off(a, b, qi), dq, a.scale, a.cs, qi, lane);
@@ -522,15 +592,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // 1 KB slot of the stage (lanes 0-7 lse, 8-15 delta, the rest repeat them).
 // To hold two workgroups of 256 registers per lane on a SIMD, the last NPARK
 // of the wave's V fragments are kept in LDS and read back for each tile.
-template <int NW, int S, bool TOK>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_kernel(AttnArgs a) {
+template <int NW, int S, bool TOK, int KS>
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_kernel(AttnArgs a) {
   constexpr int KB = NW * NB;
   constexpr int PW = 8 / NW;
   constexpr int STAGE = 2 * TILE16 + 64;  // Q, dO tiles, row terms
   constexpr int NPARK = 3;
-  __shared__ u32x4a smem[S * STAGE + NW * NPARK * 64];
+  __shared__ u32x4a smem[S * KS * STAGE + NW * KS * NPARK * 64];
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int wave = wv % NW, ks = wv / NW;
   const int L = a.L;
   int kb;
   int64_t b;
@@ -557,7 +628,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     rod[q] = row_off(wave * PW + q, lane, ldo);
   }
   bf16x8a kf[8], vf[8 - NPARK];
-  u32x4a* park = smem + S * STAGE + wave * NPARK * 64;
+  u32x4a* park = smem + S * KS * STAGE + wv * NPARK * 64;
   {
     const int64_t row = (bk * L + kc) * int64_t(D) + 8 * (lane >> 5);
 #pragma unroll
@@ -570,12 +641,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
   f32x16a dk[4] = {zero16(), zero16(), zero16(), zero16()};
   f32x16a dv[4] = {zero16(), zero16(), zero16(), zero16()};
-  const int nt = n_tiles - first;  // tiles the workgroup walks
+  const int nt = (n_tiles - first + KS - 1) / KS;  // steps of the walk, as in the forward
+  auto tile_at = [&](int i) { return KS == 1 ? first + i : min(first + i * KS + ks, n_tiles - 1); };
+  auto stage_at = [&](int i) { return smem + ((i % S) * KS + ks) * STAGE; };
 #pragma unroll
   for (int i = 0; i < S - 1; ++i)
     if (i < nt) {
-      const int t = first + i;
-      u32x4a* st = smem + (i % S) * STAGE;
+      const int t = tile_at(i);
+      u32x4a* st = stage_at(i);
       copy_tile<PW>(Qb + int64_t(t) * NB * D, ro, st, wave);
       copy_tile<PW>(dOb + int64_t(t) * NB * ldo, rod, st + TILE16, wave);
       if (wave == 0) copy16(rt_src + t * NB, 0, st + 2 * TILE16);
@@ -585,15 +658,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     else wait_tiles<2 * PW>(min(S - 2, nt - 1 - i));
     lds_wait_barrier();
     if (i + S - 1 < nt) {
-      const int u = i + S - 1, t = first + u;
-      u32x4a* st = smem + (u % S) * STAGE;
+      const int t = tile_at(i + S - 1);
+      u32x4a* st = stage_at(i + S - 1);
       copy_tile<PW>(Qb + int64_t(t) * NB * D, ro, st, wave);
       copy_tile<PW>(dOb + int64_t(t) * NB * ldo, rod, st + TILE16, wave);
       if (wave == 0) copy16(rt_src + t * NB, 0, st + 2 * TILE16);
     }
-    const int t = first + i;
-    if (t < my_first) continue;
-    const u32x4a* st = smem + (i % S) * STAGE;
+    const int t = first + i * KS + ks;
+    if (t < my_first || (KS > 1 && t >= n_tiles)) continue;
+    const u32x4a* st = stage_at(i);
     const float* rt = reinterpret_cast<const float*>(st + 2 * TILE16);  // lse[32], delta[32]
     f32x16a s = zero16(), dp = zero16();
 #pragma unroll
@@ -646,6 +719,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
     }
   }
+  if constexpr (KS == 2) {
+    lds_wait_barrier();
+    add_groups<NW>(dk, reinterpret_cast<float*>(smem), wave, ks, lane);
+    lds_wait_barrier();
+    add_groups<NW>(dv, reinterpret_cast<float*>(smem), wave, ks, lane);
+    if (ks != 0) return;
+  }
   if (!active) return;
   if (TOK && a.kv_batch == a.batch) {
     const int64_t o = tok_off(a, b, kj);
@@ -658,9 +738,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 }
 
 namespace {
-constexpr int FWD_NW = 4, FWD_S = 2;
-constexpr int DQ_NW = 4, DQ_S = 2;
-constexpr int DKV_NW = 4, DKV_S = 2;
+constexpr int NW = 4, S = 2;  // waves per group of rows, stages
+
+// Whether the walks are split: where workgroups of four waves give about one wave
+// per SIMD, and walks of up to 16 tiles or more repay the exchange.  Forward and
+// backward together, one group against two: 288 workgroups (L = 1056) 141 against
+// 114 us, 256 (L = 2048 / 1024 / 512) 227 / 127 / 76 against 173 / 106 / 70; but
+// 512 (L = 2048 / 1024) 311 / 173 against 313 / 198, 32 (L = 256) 46 against 47.
+bool split_walk(int64_t blocks, int L) { return blocks <= 320 && L >= 512; }
+
+template <typename Kern>
+void launch(Kern kern, int64_t blocks, int ks, const AttnArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(kern, dim3(unsigned(blocks)), dim3(unsigned(NW * ks * 64)), 0, st, a);
+}
 }  // namespace
 
 static void set_tok(AttnArgs& a, const AttnLaunch& q) {
@@ -676,10 +766,10 @@ hipError_t launch_attn_fwd(const AttnLaunch& q, hipStream_t st) {
   a.batch = q.batch; a.kv_batch = q.kv_batch; a.L = q.L; a.scale = q.scale;
   a.Q = q.Q; a.K = q.K; a.V = q.V; a.O_out = q.O_out; a.lse = q.lse;
   set_tok(a, q);
-  const int64_t nblk = (q.L + FWD_NW * NB - 1) / (FWD_NW * NB);
-  const dim3 grid(unsigned(nblk * q.batch));
-  if (q.tok_seqs > 0) hipLaunchKernelGGL((attn_fwd_kernel<FWD_NW, FWD_S, true>), grid, dim3(FWD_NW * 64), 0, st, a);
-  else hipLaunchKernelGGL((attn_fwd_kernel<FWD_NW, FWD_S, false>), grid, dim3(FWD_NW * 64), 0, st, a);
+  const int64_t blocks = (q.L + NW * NB - 1) / (NW * NB) * q.batch;
+  const bool tok = q.tok_seqs > 0;
+  if (split_walk(blocks, q.L)) launch(tok ? attn_fwd_kernel<NW, S, true, 2> : attn_fwd_kernel<NW, S, false, 2>, blocks, 2, a, st);
+  else launch(tok ? attn_fwd_kernel<NW, S, true, 1> : attn_fwd_kernel<NW, S, false, 1>, blocks, 1, a, st);
   return hipGetLastError();
 }
 
@@ -690,16 +780,14 @@ hipError_t launch_attn_bwd(const AttnLaunch& q, hipStream_t st) {
   a.lse = q.lse; a.delta = q.delta; a.dQ = q.dQ; a.dK = q.dK; a.dV = q.dV;
   set_tok(a, q);
   const bool tok = q.tok_seqs > 0;
-  const int64_t nq = (q.L + DQ_NW * NB - 1) / (DQ_NW * NB);
-  const dim3 gq(unsigned(nq * q.batch));
-  if (tok) hipLaunchKernelGGL((attn_bwd_dq_kernel<DQ_NW, DQ_S, true>), gq, dim3(DQ_NW * 64), 0, st, a);
-  else hipLaunchKernelGGL((attn_bwd_dq_kernel<DQ_NW, DQ_S, false>), gq, dim3(DQ_NW * 64), 0, st, a);
+  const int64_t blocks = (q.L + NW * NB - 1) / (NW * NB) * q.batch;
+  const bool split = split_walk(blocks, q.L);
+  if (split) launch(tok ? attn_bwd_dq_kernel<NW, S, true, 2> : attn_bwd_dq_kernel<NW, S, false, 2>, blocks, 2, a, st);
+  else launch(tok ? attn_bwd_dq_kernel<NW, S, true, 1> : attn_bwd_dq_kernel<NW, S, false, 1>, blocks, 1, a, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t nk = (q.L + DKV_NW * NB - 1) / (DKV_NW * NB);
-  const dim3 gk(unsigned(nk * q.batch));
-  if (tok) hipLaunchKernelGGL((attn_bwd_dkv_kernel<DKV_NW, DKV_S, true>), gk, dim3(DKV_NW * 64), 0, st, a);
-  else hipLaunchKernelGGL((attn_bwd_dkv_kernel<DKV_NW, DKV_S, false>), gk, dim3(DKV_NW * 64), 0, st, a);
+  if (split) launch(tok ? attn_bwd_dkv_kernel<NW, S, true, 2> : attn_bwd_dkv_kernel<NW, S, false, 2>, blocks, 2, a, st);
+  else launch(tok ? attn_bwd_dkv_kernel<NW, S, true, 1> : attn_bwd_dkv_kernel<NW, S, false, 1>, blocks, 1, a, st);
   return hipGetLastError();
 }
 

@@ -167,3 +167,16 @@ def test_attention_token_major_io(n_seq, H, Hkv, L):
     assert torch.equal(bits(dQ_tok), bits(dQ_ref)), "dQ"
     assert torch.equal(bits(dK_tok), bits(dK_ref)), "dK"
     assert torch.equal(bits(dV_tok), bits(dV_ref)), "dV"
+
+
+# the split walk (at most 320 workgroups of 128 rows, L from 512 on): an odd
+# number of tiles, a last workgroup of one tile, both sides of each bound
+@pytest.mark.parametrize("L,batch,kv_batch,sharp", [(512, 2, 2, 2.0), (544, 3, 1, 3.0), (1056, 2, 1, 1.0),
+                                                    (480, 4, 2, 2.0), (512, 81, 27, 1.0)])
+def test_attention_split_walk(L, batch, kv_batch, sharp):
+    test_attention_fused(L, batch, kv_batch, sharp)
+
+
+@pytest.mark.parametrize("n_seq,H,Hkv,L", [(1, 4, 2, 544), (2, 2, 2, 512)])
+def test_attention_token_major_split(n_seq, H, Hkv, L):
+    test_attention_token_major_io(n_seq, H, Hkv, L)
