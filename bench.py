@@ -533,8 +533,8 @@ def block_decoder(seed, k=3, steps=5, warmup=2, n_kv=None):
 # Kernel-name patterns of the step's four phases in rocprofv3 output.
 PHASE_PATTERNS = {
     "fq_fwd": r"fq_fwd_kernel<1, 1, [23], ",
-    "gemm_fwd": r"gemm_pp_kernel<256, \d+, [14], ",
-    "gemm_bwd": r"gemm_pp_kernel<256, 256, 2, ",
+    "gemm_fwd": r"gemm_(?:pp_kernel<256, \d+, |w4_kernel<)[14], ",
+    "gemm_bwd": r"gemm_(?:pp_kernel<256, \d+, |w4_kernel<)2, ",
     "fq_bwd": r"fq_bwd_kernel<1, 1, ",
     "fq_step": r"fq_step_kernel<1, 1, 1, [023], ",
 }

@@ -527,18 +527,19 @@ struct FoldArgs {
 };
 
 // Each wavefront owns 512 consecutive weights with their groups' tables in its
-// own LDS, as the forward does.  Up to 8 levels the nearest one is found by
+// own LDS, as the forward does.  Up to 4 levels the nearest one is found by
 // trying all of them from registers (a lane's 8 weights lie in one group), which
 // is the definition of the mapping, first of the smallest |fl(x - q_j)|, in four
-// instructions a level without the dependent LDS reads of a search; from 16
-// levels on the search is shorter.
-// 11008 x 4096, k = 3, g = 128: 75 us against 106 with workgroup-wide tables,
-// k and the levels as variables and the search (the 7 bytes a weight take 60 us).
+// instructions a level without the dependent LDS reads of a search; from 8 levels
+// on the search is shorter (k = 3: 70 us against 75 for the scan).
+// 11008 x 4096, k = 3, g = 128: 70 us against 106 with workgroup-wide tables, k and
+// the levels as variables and the weights loaded behind the tables (the 7 bytes
+// a weight take 60 us).
 template <int WDT, int LOGL>
 __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr int L = 1 << LOGL, K = LOGL;
-  constexpr bool scan = LOGL <= 3;
+  constexpr bool scan = LOGL <= 2;
   const TileGeom& g = a.t;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int gw = 512 >> g.logg;  // groups per wave
