@@ -594,11 +594,13 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
     if (a.code_src != 0) zb = p.dl * (zb - p.zu);
     tab.raw[e] = level_value_k<LOGL>(al, zb, e & (L - 1));
   };
-  if (lane < ev) put_level(lane, pe);
+  if (a.codes != nullptr) {
+    if (lane < ev) put_level(lane, pe);
+    for (int e = lane + 64; e < ev; e += 64) put_level(e, load_group(gid0 + (e >> LOGL), false));
+  }
+  // past every read of the wavefront's parameters, which the results may overwrite
   if (lane < gv) put_group(lane, pg);
-  for (int gl = lane + 64; gl < gv; gl += 64) put_group(gl, load_group(gid0 + gl, true));
   if (a.codes == nullptr) return;  // uniform across the grid
-  for (int e = lane + 64; e < ev; e += 64) put_level(e, load_group(gid0 + (e >> LOGL), false));
   wave_lds_sync();
   for (int e = lane; e < ev; e += 64) {
     const int b = e & (L - 1), base = e - b;

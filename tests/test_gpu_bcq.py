@@ -206,3 +206,24 @@ def test_fold_edges(R, C, k, g, code_src):
         assert np.array_equal(cd.cpu().numpy().reshape(R, C), fo["codes"])
         assert np.array_equal(a_st.cpu().numpy(), fo["alpha_star"].reshape(-1))
         assert np.array_equal(z_st.cpu().numpy(), fo["z_star"].reshape(-1))
+
+
+# parameters written over their own inputs (Theorem 1's levels from alpha, z_B
+# in place): more levels a wavefront than lanes, and fewer; Eq. (4)'s mapping
+@pytest.mark.parametrize("R,C,k,g", [(4, 512, 4, 8), (3, 264, 7, 8), (2, 1024, 6, 64), (5, 384, 3, 128)])
+def test_fold_in_place(R, C, k, g):
+    rs = np.random.default_rng(R + C + k)
+    Gn = R * C // g
+    W = (rs.standard_normal((R, C)) * 0.3).astype(F32)
+    alpha = rs.uniform(0.1, 2.0, (Gn, k)).astype(F32)
+    delta = rs.uniform(0.01, 0.2, Gn).astype(F32)
+    z_u, z_b = (rs.standard_normal(Gn).astype(F32) for _ in range(2))
+    fo = U.fold(W, np.ones_like(W), alpha, z_b, k, g, None, delta, z_u, 1)
+    a, z = dev(alpha.reshape(-1), torch.float32), dev(z_b, torch.float32)
+    cd = torch.empty(R * C, dtype=torch.uint8, device=DEV)
+    uq.uniquan_fold_to_bcq(R, C, k, g, dev(W, torch.float32), None, None, dev(delta, torch.float32),
+                           dev(z_u, torch.float32), a, z, a, z, cd, 1)
+    torch.cuda.synchronize()
+    assert np.array_equal(cd.cpu().numpy().reshape(R, C), fo["codes"])
+    assert np.array_equal(a.cpu().numpy(), fo["alpha_star"].reshape(-1))
+    assert np.array_equal(z.cpu().numpy(), fo["z_star"].reshape(-1))
