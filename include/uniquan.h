@@ -714,7 +714,11 @@ uq_status uniquan_bcq_pack(int64_t R, int64_t C, int k, int g,
  * the sum over columns whose bit i is set), P_i from 16-entry subset-sum
  * tables of 4 activations for T <= 3 of large layers and from bf16 MFMA
  * products of the activations with the planes otherwise; fp32 accumulation,
- * deterministic order.
+ * deterministic order.  In every form a column whose bit is clear is left out
+ * of P_i exactly, so an activation of any size at a weight with every bit clear
+ * enters as (z* - sum_i alpha*_i) x only, and an infinite one gives an
+ * infinity unless a term of the other sign meets it (NaN then).  Activations of
+ * 2^32 or more and non-finite ones are slow in the MFMA form.
  * partials_ws [partials_len] fp32 workspace of at least
  * uniquan_bcq_matmul_ws(T, R, C) floats (0: may be NULL).
  */

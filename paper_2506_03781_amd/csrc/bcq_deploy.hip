@@ -283,37 +283,39 @@ typedef float f32x4b __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_a8 __attribute__((aligned(8)));  // activations are 8-byte aligned
 
 // The same product on MFMA (v_mfma_f32_16x16x32_bf16), for batches of four
-// rows on and for small layers.  Per 128-column quad and plane, with B_i the
-// plane's bits, the matrix cores sum columns' x b (tokens as M, 16 weight rows
-// as N) and y += 2 alpha*_i P_i + (z* - sum_i alpha*_i) S as above.
+// rows on and for small layers.  Per 128-column quad and plane the matrix cores
+// sum the columns whose bit is set (tokens as M, 16 weight rows as N) and
+// y += 2 alpha*_i P_i + (z* - sum_i alpha*_i) S as above.
 //
 // What bounds it is vector issue: every weight bit becomes a 16-bit operand.  A
 // lane holds one 32-column word of a row and plane, and the columns of a
 // fragment may come in any order that the activations share, so dword e of
 // fragment s pairs columns b and b + 16, b = 15 - 4 s - e: with the word
-// shifted left by 4 s, their bits stand at 15 - e of the dword's two halves, and
-// one v_and_or_b32 makes both bf16 values, whatever the bit's position:
-//   e = 0  the sign:              1/2 - b
-//   e = 1  exponent bit 7:        -2 b (0 or -2; the activations are halved)
-//   e = 2  exponent bit 6:        -b   (-2^-64 for 0)
-//   e = 3  exponent bit 5:        -b   (-2^-32 for 0, 2^8 below fp32's rounding)
-// 16 and three shifts per word and plane, where a 256-entry table in LDS was
-// bound by its 16-byte reads.  The sums come as S_0 / 2 - P_i with S_0 the
-// activation sum of the sign columns; one more product with constant columns
-// gives S and S - S_0, and the kernel keeps y / 2 so that no factor is applied
-// twice:  y / 2 = sum [ z S / 2 - asum (S - S_0) / 2 - sum_i alpha*_i (S_0 / 2 - P_i) ].
+// shifted left by 4 s - 1, their bits stand at 14 - e of the dword's two halves,
+// and one v_and_b32 makes both bf16 values: 0, exactly, for a clear bit and a
+// power of two for a set one, 2^1, 2^-63, 2^-95, 2^-111 for e = 0 .. 3.  The
+// activations carry the rest (kUnit 2^-1, 2^63, ..): the products are kUnit x b,
+// exactly, and one more product with constant columns gives kUnit S.  16
+// instructions and four shifts per word and plane, where a 256-entry table in
+// LDS was bound by its 16-byte reads.  (Bits expanded as (w & mask) | constant, the
+// sign among them, took a shift less, but left a clear bit +-1/2, 2^-32 or
+// 2^-64 of its activation.)
+// An activation of 2^32 or more (or not finite) overflows its scaling, and what
+// comes out not finite is added up again column by column (bcq_plain_sum).
 //
 // A wavefront takes 16 RT rows of its quads; the W wavefronts of a workgroup
 // split the quads of the same rows and add up in LDS in a fixed order, so that
 // most shapes need no partial rows and no second launch.  Each wavefront loads
-// its quad's activations once, coalesced, pairs and halves them and reads the
+// its quad's activations once, coalesced, pairs and scales them and reads the
 // fragments back from its own LDS region (fragments loaded from memory touched
 // 64 lines an instruction and were the bound: 58 us).  With RT = 2 a plane is
 // one 8-byte load per lane, and v_permlane32_swap sorts words and parameters
 // to the two row tiles.
-// Measured (T = 8, g = 128): 28672 x 8192, k = 3: 38 us against 44 for the
-// table-expanded 32 x 32 x 16 form with partial rows; 8192 x 28672: 36 against
-// 44; 4096 x 4096, k = 4: 7.2 against 10.2 (one launch instead of two).
+// Measured (T = 8, g = 128; the table-expanded 32 x 32 x 16 form with partial rows
+// before): 28672 x 8192, k = 3: 37 us against 45; 8192 x 28672: 34 against 45;
+// 4096 x 4096, k = 4: 6.8 against 9.5 (one launch instead of two).  With the signed
+// expansion 38, 35 and 6.7; its error against 64 bits was 1.3e-7, now 1.2e-7.
+//
 // One 128-column quad of 16 RT rows as a wavefront loads it: plane words,
 // parameters (binary16) and this lane's 32 activations.
 template <int K, int RT>
@@ -322,6 +324,40 @@ struct BcqQuad {
   uint16_t a[K], z;
   u32x4 x[2];
 };
+
+constexpr float kUnit = 0x1p-15f;
+
+// Token tok's product with row r over quads q .. q_end - 1, one column at a time:
+// the definition, for what overflows a fragment.  An infinite activation enters
+// the sums of the bits that are set at its column and no others.
+template <int K>
+__device__ __forceinline__ float bcq_plain_sum(const BcqArgs& a, int tok, int64_t r, int64_t q, int64_t q_end) {
+  float y = 0.0f;
+  for (; q < q_end; ++q) {
+    const int64_t j = q / a.qpg;
+    float S = 0.0f, P[K] = {}, asum = 0.0f;
+    for (int m = 0; m < 4; ++m) {
+      uint32_t w[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) w[i] = a.planes[((i * a.nq + q) * a.R + r) * 4 + m];
+      for (int c = 0; c < 32; ++c) {
+        const float x = bf16_to_f32(a.X[tok * a.C + q * 128 + 32 * m + c]);
+        S += x;
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+          if ((w[i] >> c) & 1u) P[i] += x;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const float av = f16_to_f32(a.alpha16[(i * a.gpr + j) * a.R + r]);
+      asum += av;
+      y = __builtin_fmaf(2.0f * av, P[i], y);
+    }
+    y = __builtin_fmaf(f16_to_f32(a.z16[j * a.R + r]) - asum, S, y);
+  }
+  return y;
+}
 
 // Workgroup (bx, by): the 16 RT rows of row block rb0 + bx, quads qps by .. + qps - 1;
 // wavefront w takes every W-th of them.
@@ -369,23 +405,17 @@ __global__ __launch_bounds__(64 * W) void bcq_mfma_kernel(BcqArgs a, int T) {
     d.x[1] = *reinterpret_cast<const u32x4_a8*>(at(xq + 16, xoff));
   };
 
-  // columns n even: 1/2 on every column, n odd: 1/2 on all but the sign slots
-  constexpr uint32_t HALF = 0x3F003F00u;
-  const u32x4 sums = {(n & 1) ? 0u : HALF, 0x3F803F80u, HALF, HALF};  // (slot 1 holds x / 2)
+  constexpr uint32_t m[4] = {0x40004000u, 0x20002000u, 0x10001000u, 0x08000800u};
+  const u32x4 sums = {m[0], m[1], m[2], m[3]};
+  constexpr float scale[4] = {0.5f * kUnit, 0x1p63f * kUnit, 0x1p95f * kUnit, 0x1p111f * kUnit};
   f32x4b y[RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t) y[t] = f32x4b{0.0f, 0.0f, 0.0f, 0.0f};
 
-  // Bits as bf16 (the two halves of a dword at once): constants the compiler
-  // keeps in registers, so that (w & m) | c is one v_and_or_b32 (as literals
-  // they make it two instructions).
-  uint32_t m[4] = {0x80008000u, 0x40004000u, 0x20002000u, 0x10001000u};
-  uint32_t c[4] = {HALF, 0x80008000u, 0x9F809F80u, 0xAF80AF80u};
-  asm("" : "+s"(m[0]), "+s"(m[1]), "+s"(m[2]), "+s"(m[3]));
-  asm("" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
-
   auto mul = [&](BcqQuad<K, RT>& d) {
-    // chunk s, dword e: columns b and b + 16 of the word, b = 15 - 4 s - e
+    // chunk s, dword e: columns b and b + 16 of the word, b = 15 - 4 s - e.  (An odd
+    // column's fp32 value keeps the even one's bits below it: they are cut off
+    // again, and where the odd one is 0 they are worth less than 2^-133.)
     bf16x8b xa[4];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -393,20 +423,20 @@ __global__ __launch_bounds__(64 * W) void bcq_mfma_kernel(BcqArgs a, int T) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int i = (7 - 4 * h - e) >> 1;
-        v[e] = __builtin_amdgcn_perm(d.x[1][i], d.x[0][i], (e & 1) ? 0x05040100u : 0x07060302u);
+        const uint32_t x0 = (e & 1) ? d.x[0][i] << 16 : d.x[0][i], x1 = (e & 1) ? d.x[1][i] << 16 : d.x[1][i];
+        v[e] = __builtin_amdgcn_perm(__float_as_uint(__uint_as_float(x1) * scale[e]),
+                                     __float_as_uint(__uint_as_float(x0) * scale[e]), 0x07060302u);
       }
-      const float lo = __uint_as_float(v[1] << 16) * 0.5f, hi = __uint_as_float(v[1] & 0xFFFF0000u) * 0.5f;
-      v[1] = __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
       xput[h] = v;
     }
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): written (read by this wavefront only)
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int s = 0; s < 4; ++s) xa[s] = __builtin_bit_cast(bf16x8b, xget[s]);
-    f32x4b Sm = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4b S = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      Sm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[s], __builtin_bit_cast(bf16x8b, sums), Sm, 0, 0, 0);
+      S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[s], __builtin_bit_cast(bf16x8b, sums), S, 0, 0, 0);
     uint32_t al[K][RT], zz[RT];
 #pragma unroll
     for (int i = 0; i < K; ++i) {
@@ -426,13 +456,6 @@ __global__ __launch_bounds__(64 * W) void bcq_mfma_kernel(BcqArgs a, int T) {
       zz[0] = zv[0];
       zz[1] = zv[1];
     }
-    f32x4b S, Se;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {  // quad_perm [0, 0, 2, 2] and [1, 1, 3, 3]
-      const int v = __float_as_int(Sm[r]);
-      S[r] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xA0, 0xF, 0xF, true));
-      Se[r] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xF5, 0xF, 0xF, true));
-    }
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
       const float z = f16_to_f32(uint16_t(zz[t]));
@@ -444,16 +467,15 @@ __global__ __launch_bounds__(64 * W) void bcq_mfma_kernel(BcqArgs a, int T) {
         f32x4b P = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const uint32_t w = d.w[i][t] << (4 * s);
-          const u32x4 b = {(w & m[0]) | c[0], (w & m[1]) | c[1], (w & m[2]) | c[2], (w & m[3]) | c[3]};
+          const uint32_t w = s == 0 ? d.w[i][t] >> 1 : d.w[i][t] << (4 * s - 1);
+          const u32x4 b = {w & m[0], w & m[1], w & m[2], w & m[3]};
           P = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[s], __builtin_bit_cast(bf16x8b, b), P, 0, 0, 0);
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) y[t][r] = __builtin_fmaf(-av, P[r], y[t][r]);
+        for (int r = 0; r < 4; ++r) y[t][r] = __builtin_fmaf(2.0f * av, P[r], y[t][r]);
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        y[t][r] = __builtin_fmaf(z, S[r], __builtin_fmaf(-asum, Se[r], y[t][r]));
+      for (int r = 0; r < 4; ++r) y[t][r] = __builtin_fmaf(z - asum, S[r], y[t][r]);
     }
   };
 
@@ -481,7 +503,7 @@ __global__ __launch_bounds__(64 * W) void bcq_mfma_kernel(BcqArgs a, int T) {
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave][4 * kg + r][16 * t + n] = 2.0f * y[t][r];
+      for (int r = 0; r < 4; ++r) red[wave][4 * kg + r][16 * t + n] = (1.0f / kUnit) * y[t][r];
   }
   __syncthreads();
   const int tok = threadIdx.x / ROWS, rr = threadIdx.x % ROWS;
@@ -489,6 +511,7 @@ __global__ __launch_bounds__(64 * W) void bcq_mfma_kernel(BcqArgs a, int T) {
     float s = 0.0f;
 #pragma unroll
     for (int w = 0; w < W; ++w) s += red[w][tok][rr];
+    if (!(fabsf(s) < INFINITY)) s = bcq_plain_sum<K>(a, tok, r0 + rr, int64_t(blockIdx.y) * a.qps, q_end);
     a.out[(int64_t(blockIdx.y) * T + tok) * R + r0 + rr] = s;
   }
 }

@@ -227,3 +227,63 @@ def test_fold_in_place(R, C, k, g):
     assert np.array_equal(cd.cpu().numpy().reshape(R, C), fo["codes"])
     assert np.array_equal(a.cpu().numpy(), fo["alpha_star"].reshape(-1))
     assert np.array_equal(z.cpu().numpy(), fo["z_star"].reshape(-1))
+
+
+def expected_terms(X, codes, a, z, g):
+    """Y as the product is defined in the header, column by column in fp64: z* - sum_i alpha*_i for every column
+    and 2 alpha*_i where bit i is set, the columns whose bit is clear left out of the second."""
+    k = a.shape[1]
+    R, C = codes.shape
+    a16, z16 = (v.astype(np.float16).astype(np.float64) for v in (a.reshape(R, C // g, k), z.reshape(R, C // g)))
+    Xd = X.astype(np.float64)
+    base = np.repeat(z16 - a16.sum(2), g, axis=1)  # [R, C]
+    Y = np.zeros((X.shape[0], R))
+    with np.errstate(invalid="ignore"):
+        for t in range(X.shape[0]):
+            Y[t] = (Xd[t][None, :] * base).sum(1)
+            for i in range(k):
+                bit = ((codes >> i) & 1) == 1
+                Y[t] += np.where(bit, 2.0 * np.repeat(a16[:, :, i], g, axis=1) * Xd[t][None, :], 0.0).sum(1)
+    return Y
+
+
+# both forms (layers of up to 21 M weights with few rows, larger ones), 16- and 32-row workgroups
+EXTREME = [(1, 100, 512, 2, 128), (2, 40, 1152, 3, 384), (3, 8200, 512, 1, 128), (8, 33, 640, 4, 640), (5, 8193, 256, 2, 128),
+           (2, 5001, 4224, 1, 128)]
+
+
+@pytest.mark.parametrize("T,R,C,k,g", EXTREME)
+def test_matmul_columns_of_level_zero(T, R, C, k, g):
+    """Activations of 2^40 on columns whose weight is exactly 0 (every bit clear, z* = sum_i alpha*_i) leave no trace:
+    the other terms are small multiples of 1/4, so the sums are exact."""
+    rs = np.random.default_rng(T + R + C)
+    codes = synth.random_codes(R, C, k, 40)
+    a = np.tile(np.array([0.25, 0.5, 1.0, 2.0], F32)[:k], (R * C // g, 1))
+    z = a.sum(1)
+    X = rs.integers(-4, 5, (T, C)).astype(F32)
+    big = rs.permutation(C)[:C // 3]
+    codes[:, big] = 0
+    X[:, big] = (2.0 ** 40 * rs.choice([-1.0, 1.0], (T, big.size))).astype(F32)
+    Y = gpu_matmul(T, R, C, k, g, X, gpu_pack(codes, a, z, k, g))
+    assert np.array_equal(Y.astype(np.float64), expected_terms(X, codes, a, z, g))
+
+
+@pytest.mark.parametrize("T,R,C,k,g", EXTREME)
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 2.0 ** 100])
+def test_matmul_extreme_activations(T, R, C, k, g, bad):
+    """An infinite, NaN or very large activation enters with its weight: columns whose bit is clear are left out of
+    the bit's sum, so that an infinity comes out with its sign where no set bit opposes it; other rows of X are as
+    they would be without it."""
+    codes, a, z, X = inputs(T, R, C, k, g, 41)
+    z = (z - 0.3).astype(F32)  # z* below every sum of scales: a clear column's weight is negative, far from 0
+    st = gpu_pack(codes, a, z, k, g)
+    clean = gpu_matmul(T, R, C, k, g, X, st)
+    X[T - 1, C - 7] = bad
+    Y = gpu_matmul(T, R, C, k, g, X, st)
+    assert np.array_equal(Y[:T - 1].view(np.uint32), clean[:T - 1].view(np.uint32))
+    ref = expected_terms(X[T - 1:], codes, a, z, g)[0]
+    y = Y[T - 1].astype(np.float64)
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
+    assert np.array_equal(np.sign(y[np.isinf(y)]), np.sign(ref[np.isinf(ref)]))
+    f = np.isfinite(ref)
+    assert np.all(np.abs(y[f] - ref[f]) <= 1e-5 * np.abs(ref[f]).max(initial=0.0))
