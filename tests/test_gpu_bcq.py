@@ -105,26 +105,38 @@ def test_matmul(T, R, C, k, g):
     assert np.array_equal(gpu_matmul(T, R, C, k, g, X, st).view(np.uint32), Y.view(np.uint32))
 
 
-def sampled(T, R, C, k, g, seed, n_rows):
+def sampled(T, R, C, k, g, seed, n_rows, last=False):
     codes, a, z, X = inputs(T, R, C, k, g, seed)
     Y = gpu_matmul(T, R, C, k, g, X, gpu_pack(codes, a, z, k, g))
-    rows = np.sort(np.random.default_rng(seed).choice(R, n_rows, replace=False))
+    rows = np.sort(np.random.default_rng(seed).choice(R - int(last), n_rows - int(last), replace=False))
+    if last:
+        rows = np.append(rows, R - 1)
     gpr = C // g
     gidx = (rows[:, None] * gpr + np.arange(gpr)[None, :]).reshape(-1)
     ref = D.matmul_f64(X, *D.pack(codes[rows], a[gidx], z[gidx], k, g), n_rows, C, g)
     close(Y[:, rows], ref, f"sampled rows {R}x{C}")
 
 
-def test_matmul_wide_tables():
-    """8 batch rows and 4 quads per slab (the MFMA form)."""
+def test_matmul_eight_rows():
+    """8 batch rows, 64 column quads (8 a wavefront; MFMA form)."""
     sampled(8, 8192, 8192, 4, 128, 21, 64)
 
 
 @pytest.mark.parametrize("T", [3, 6])
 def test_matmul_partial_last_slab(T):
-    """33 column quads at 2 per slab: the last slab holds one quad (table
-    form at 3 batch rows, MFMA form at 6)."""
+    """33 column quads: at 2 per slab (table form, 3 batch rows) the last slab
+    holds one; at one per wavefront and turn (MFMA form, 6 rows) the last turn does."""
     sampled(T, 8192, 4224, 3, 128, 25, 48)
+
+
+# the table form (1 to 3 batch rows of layers above 21 M weights): 1, 2 and 4
+# quads a slab, the last slab of 33 quads short, groups of 2, 3, 11 and 16 quads
+# and of a whole row, last row blocks of one row and of 137
+@pytest.mark.parametrize("T,R,C,k,g", [(1, 5001, 4224, 1, 384), (2, 5001, 4224, 2, 4224), (3, 5001, 4224, 4, 128),
+                                       (2, 8193, 4224, 4, 1408), (1, 8193, 4224, 2, 128), (3, 8193, 4224, 1, 384),
+                                       (1, 8193, 8192, 4, 8192), (2, 8193, 8192, 1, 256), (3, 8193, 8192, 2, 2048)])
+def test_matmul_table_form(T, R, C, k, g):
+    sampled(T, R, C, k, g, 33, 48, last=True)
 
 
 # the MFMA form's dispatch: 16-row and 32-row workgroups with a ragged last one,
@@ -253,8 +265,9 @@ EXTREME = [(1, 100, 512, 2, 128), (2, 40, 1152, 3, 384), (3, 8200, 512, 1, 128),
 
 
 @pytest.mark.parametrize("T,R,C,k,g", EXTREME)
-def test_matmul_columns_of_level_zero(T, R, C, k, g):
-    """Activations of 2^40 on columns whose weight is exactly 0 (every bit clear, z* = sum_i alpha*_i) leave no trace:
+@pytest.mark.parametrize("big_x", [2.0 ** 30, 2.0 ** 40])  # below and above what the MFMA form's scaling takes
+def test_matmul_columns_of_level_zero(T, R, C, k, g, big_x):
+    """Large activations on columns whose weight is exactly 0 (every bit clear, z* = sum_i alpha*_i) leave no trace:
     the other terms are small multiples of 1/4, so the sums are exact."""
     rs = np.random.default_rng(T + R + C)
     codes = synth.random_codes(R, C, k, 40)
@@ -263,7 +276,7 @@ def test_matmul_columns_of_level_zero(T, R, C, k, g):
     X = rs.integers(-4, 5, (T, C)).astype(F32)
     big = rs.permutation(C)[:C // 3]
     codes[:, big] = 0
-    X[:, big] = (2.0 ** 40 * rs.choice([-1.0, 1.0], (T, big.size))).astype(F32)
+    X[:, big] = (big_x * rs.choice([-1.0, 1.0], (T, big.size))).astype(F32)
     Y = gpu_matmul(T, R, C, k, g, X, gpu_pack(codes, a, z, k, g))
     assert np.array_equal(Y.astype(np.float64), expected_terms(X, codes, a, z, g))
 

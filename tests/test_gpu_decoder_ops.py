@@ -529,6 +529,35 @@ def test_gemm_pp_triangular_vs_fp64(mode, tri):
         assert np.all(np.abs(g1[b] - ref) <= 1e-5 * mag + 1e-30), (mode, b)
 
 
+# 256 x 256 tiles (N above 128, at least 256 of them with the batch): the k range of a row of tiles starts or
+# ends at its diagonal, K a multiple of 64 and not
+@pytest.mark.parametrize("L,batch", [(1024, 32), (736, 43)])
+@pytest.mark.parametrize("mode,tri", [(2, np.tril), (3, np.triu)])
+def test_gemm_wide_triangular_vs_fp64(L, batch, mode, tri):
+    N = 264
+    rs = np.random.default_rng(L + mode)
+    A, dA = _bf16_dev(rs, (batch, L, L), tri)
+    B, dB = _bf16_dev(rs, (batch, N, L))
+    O0 = torch.zeros(batch, L, N, device="cuda")
+    O1 = torch.full((batch, L, N), 7.0, device="cuda")
+    uq.uniquan_gemm_nt_batched(L, N, L, batch, dA, L * L, dB, N * L, O0, L * N, 1.0, 0)
+    uq.uniquan_gemm_nt_batched(L, N, L, batch, dA, L * L, dB, N * L, O1, L * N, 1.0, mode)
+    torch.cuda.synchronize()
+    g0, g1 = host(O0), host(O1)
+    assert np.array_equal(g0, g1)
+    for b in range(0, batch, 7):
+        ref = A[b] @ B[b].T
+        mag = np.abs(A[b]) @ np.abs(B[b]).T
+        assert np.all(np.abs(g1[b] - ref) <= 1e-5 * mag + 1e-30), (mode, b)
+
+
+# K no multiple of 32 in a batch: 128 x 128, 256 x 128 and 256 x 256 tiles, with a shared operand
+@pytest.mark.parametrize("M,N,batch,sb", [(72, 136, 3, 1), (300, 520, 27, 0), (520, 264, 43, 1)])
+@pytest.mark.parametrize("K", [40, 72, 200])
+def test_gemm_nt_batched_any_k(M, N, K, batch, sb):
+    test_gemm_nt_batched(M, N, K, batch, 1, sb)
+
+
 @pytest.mark.parametrize("n_seq,L,H,G,nsum", [(2, 8, 4, 2, 2), (2, 64, 8, 4, 4)])
 def test_rope_grouped_slots_and_partial_sums(n_seq, L, H, G, nsum):
     """Grouped slot order (head h at (h mod G) (H / G) + h / G) and the merge
