@@ -1156,8 +1156,17 @@ __device__ __forceinline__ void static_for(const F& f) {
   }
 }
 
+// A 4-pass MFMA's registers are written 16 cycles after it has issued, 7 wait
+// states before another instruction than an MFMA may read them, and the compiler
+// cannot see that of one in asm.  So the last products of a stage are no asm
+// (SEEN): whatever follows, copies that the register allocator puts behind the
+// loop among them, the compiler waits for those three, and the others have been
+// followed by three products.  (An s_nop behind the loop is no guard, since such
+// copies may come before it; one in every stage took 1% of the 7B block's step.)
+template <bool SEEN>
 __device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& a, const bf16x8& b) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  if constexpr (SEEN) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const uint16_t* base) {
@@ -1322,7 +1331,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w4_kernel(GemmArgs p) {
         __builtin_amdgcn_sched_barrier(0);
       }
       constexpr int s = n / 64, i = (n % 64) / F, j = n % F;
-      mfma16(acc[i][j], fa[s][i], fb[s][j]);
+      mfma16<n % 64 >= 61>(acc[i][j], fa[s][i], fb[s][j]);
       if constexpr (n < kBar1 && n % kRead1 == 0 && n / kRead1 < 2 * F) read(st, 1, n / kRead1);
       if constexpr (n >= kBar1 && (n - kBar1) % kCopy == 0 && (n - kBar1) / kCopy < PW)
         copy(st, a2, b2, u2, (n - kBar1) / kCopy);
@@ -1334,7 +1343,6 @@ __global__ __launch_bounds__(256, 1) void gemm_w4_kernel(GemmArgs p) {
     b1 = b2;
     u1 = u2;
   }
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last MFMAs have written their registers
   wait_vmcnt<0>();   // the reloads past the end have landed
   __syncthreads();   // every wave is past its last operand read: the stages become epilogue scratch
   epilogue<BM, BN, EPI, 128, 128>(p, acc, m0, n0, wm, wn, lane, wave, tid, reinterpret_cast<float*>(smem));
