@@ -327,11 +327,15 @@ __device__ __forceinline__ void write_strip(const f32x4 (&acc)[FM][FN], int i, i
 // one 32-row strip at a time: each wave writes its strip (32 x WN fp32) to its
 // own LDS region, then reads it back as rows of float4 so that the target is
 // loaded and the output stored as contiguous 16-byte / 8-byte vectors.
-// `scratch` must hold NW * (32 * WN + 1) floats and may alias the operand stages
-// (all waves are past their last operand read when this is called).
-template <int BM, int BN, int EPI, int WM = BM / 2, int WN = BN / 2, int NW = 4, typename Acc>
+// `lds` holds the strips (and a float per wave for the losses) and may be the
+// operand stages (all waves are past their last operand read when this is called).
+constexpr bool is_loss(int epi) { return epi == EPI_LOSS || epi == EPI_LOSS_RES || epi == EPI_LOSS_BLOCK; }
+
+template <int BM, int BN, int EPI, int WM = BM / 2, int WN = BN / 2, int NW = 4, typename Acc, size_t NS>
 __device__ __forceinline__ void epilogue(const GemmArgs& p, const Acc& acc, int64_t m0, int64_t n0, int wm, int wn,
-                                         int lane, int wave, int tid, float* scratch) {
+                                         int lane, int wave, int tid, uint4 (&lds)[NS]) {
+  static_assert(NS * 4 >= size_t(NW) * (32 * WN + (is_loss(EPI) ? 1 : 0)), "strips, and the loss sums past them");
+  float* scratch = reinterpret_cast<float*>(lds);
   constexpr int Q = WN / 4;            // float4 per strip row
   constexpr int ITER = 32 * Q / 64;    // float4 per lane per strip
   float* strip = scratch + wave * 32 * WN;
@@ -457,7 +461,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& p, const Acc& acc, int6
       const int64_t o = base + rr * ldn + cc;
       if constexpr (EPI == EPI_TARGET) {
         *reinterpret_cast<float4*>(static_cast<float*>(p.out) + o) = v;
-      } else if constexpr (EPI == EPI_LOSS || EPI == EPI_LOSS_RES || EPI == EPI_LOSS_BLOCK) {
+      } else if constexpr (is_loss(EPI)) {
         float e0 = v.x, e1 = v.y, e2 = v.z, e3 = v.w;
         if constexpr (EPI == EPI_LOSS) {
           e0 = v.x - y[it].x;
@@ -501,7 +505,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& p, const Acc& acc, int6
     __builtin_amdgcn_s_waitcnt(0xC07F);  // strip reads done before the next strip overwrites it
     __builtin_amdgcn_wave_barrier();
   }
-  if constexpr (EPI == EPI_LOSS || EPI == EPI_LOSS_RES || EPI == EPI_LOSS_BLOCK) {
+  if constexpr (is_loss(EPI)) {
     // past the strips: a second LDS object would make the compiler wait for
     // every copy in flight before each of the main loop's LDS reads
     float* sred = scratch + NW * 32 * WN;
@@ -682,7 +686,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs p) {
     __syncthreads();
   }
 
-  epilogue<BM, BN, EPI>(p, acc, m0, n0, wm, wn, lane, wave, tid, reinterpret_cast<float*>(smem));
+  epilogue<BM, BN, EPI>(p, acc, m0, n0, wm, wn, lane, wave, tid, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -872,7 +876,7 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmArgs p) {
     interleave();
   }
   __syncthreads();  // every wave is past its last operand read: the stages become epilogue scratch
-  epilogue<BM, BN, EPI>(p, acc, m0, n0, wm, wn, lane, wave, tid, reinterpret_cast<float*>(smem));
+  epilogue<BM, BN, EPI>(p, acc, m0, n0, wm, wn, lane, wave, tid, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1110,7 +1114,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
   if (grp == 0) __builtin_amdgcn_s_barrier();
   wait_vmcnt<0>();   // the reloads past the end have landed
   __syncthreads();   // every wave is past its last operand read: the stages become epilogue scratch
-  epilogue<BM, BN, EPI, WM, WN, 8>(p, acc, m0, n0, wm, wn, lane, wave, tid, reinterpret_cast<float*>(smem));
+  epilogue<BM, BN, EPI, WM, WN, 8>(p, acc, m0, n0, wm, wn, lane, wave, tid, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1345,7 +1349,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w4_kernel(GemmArgs p) {
   }
   wait_vmcnt<0>();   // the reloads past the end have landed
   __syncthreads();   // every wave is past its last operand read: the stages become epilogue scratch
-  epilogue<BM, BN, EPI, 128, 128>(p, acc, m0, n0, wm, wn, lane, wave, tid, reinterpret_cast<float*>(smem));
+  epilogue<BM, BN, EPI, 128, 128>(p, acc, m0, n0, wm, wn, lane, wave, tid, smem);
 }
 
 template <int BM, int BN>
