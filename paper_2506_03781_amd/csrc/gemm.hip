@@ -1382,19 +1382,47 @@ size_t gemm_workgroups(int64_t M, int64_t N, int /*epi*/) {
 // conditions on K).
 static bool deep_takes(const GemmArgs& a) { return a.K >= 64 && (a.causal == 0 || a.K % 64 == 0); }
 
-// Whether 256 x 256 tiles go to the four-wavefront kernel: 64-deep stages, and
-// byte offsets within a stage below 2^32.  It is the faster one on every shape
-// measured (by 18-30%).
+// Whether gemm_w4_kernel takes the shape: 64-deep stages, and byte offsets
+// within a stage below 2^32.
 static bool w4_takes(const GemmArgs& a, bool ta, bool tb) {
   return deep_takes(a) && a.K <= (int64_t(1) << 22) && (!ta || a.M <= (int64_t(1) << 24)) &&
          (!tb || a.N <= (int64_t(1) << 24));
 }
 
-// 256 x 256 tiles on the four-wavefront kernel where it takes the shape, else
-// on the ping-pong kernel with WAVES_M wavefront rows (K % 32 == 0).
+// The K from which gemm_w4_kernel is the faster one.  It multiplies 15-20% faster,
+// but starts later and stores with half the wavefronts of the ping-pong kernel: 1 us
+// where a store is a copy, 3 us with the heads' rotation, 4 with the SiLU
+// product, 8-9 with its backward and 20-30 with the straight-through backward.
+// With fewer tiles than CUs (full == false) nothing hides the store, and the products'
+// own lead is smaller (fewer CUs draw less power).  Time against the ping-pong
+// kernel's on both sides of each line:
+//   stores, residual, block loss, loss without a target: K = 256 0.96-1.08, 512 0.92-1.02
+//   loss against an fp32 target:                         K = 768 0.96-1.03, 1024 0.93-0.98
+//   heads:           full K = 1024 0.99-1.00, 1280 0.97-0.99; else 2048 1.00-1.04, 2560 0.99
+//   SiLU product:    full K = 768 0.99-1.00, 1024 0.94-0.96; else 1536 1.01-1.03, 2048 0.97-1.00
+//   its backward:    full K = 2048 1.02-1.05, 2560 0.98; else 4096 1.01-1.02, 5120 0.97
+//   straight-through backward: K = 5120 0.98-1.02, 6144 0.97
+template <int EPI>
+constexpr int64_t w4_depth(bool full) {
+  if (EPI >= EPI_STE) return 6144;
+  switch (EPI) {
+    case EPI_LOSS: return 1024;
+    case EPI_HEADS:
+    case EPI_HEADS_ROT: return full ? 1280 : 2560;
+    case EPI_SWIGLU: return full ? 1024 : 2048;
+    case EPI_SWIGLU_BWD: return full ? 2560 : 5120;
+    default: return 512;
+  }
+}
+
+// 256 x 256 tiles: on the four-wavefront kernel where it takes the shape and K is
+// deep enough for it (or no multiple of 32), else on the ping-pong kernel with
+// WAVES_M wavefront rows.  Causal modes 2 and 3 walk half of K on average.
 template <int EPI, int WAVES_M = 2, bool TA = false, bool TB = false>
 static void launch_256(const GemmArgs& a, dim3 grid, hipStream_t st) {
-  if (w4_takes(a, TA, TB))
+  const bool full = int64_t(grid.x) * grid.y >= 256;
+  const int64_t depth = a.causal >= 2 ? a.K / 2 : a.K;
+  if (w4_takes(a, TA, TB) && (a.K % 32 != 0 || depth >= w4_depth<EPI>(full)))
     hipLaunchKernelGGL((gemm_w4_kernel<EPI, TA, TB>), grid, dim3(256), 0, st, a);
   else
     hipLaunchKernelGGL((gemm_pp_kernel<256, 256, EPI, WAVES_M, 32, TA, TB>), grid, dim3(512), 0, st, a);

@@ -1,7 +1,7 @@
-"""The 256 x 256 tile product (K a multiple of 64) at the edges of its range:
-one, two, three and five 64-deep stages, ragged rows and columns, every operand
-layout.  Against an fp64 product, and bit for bit against the same product with
-32 zero columns appended to K, which runs with a short first stage (the added
+"""Products on 256 x 256 tiles: a few stages (the ping-pong kernel) and K from
+which the four-wavefront kernel takes them, whole and short first stages, ragged
+rows and columns, every operand layout and epilogue.  Against an fp64 product, and
+bit for bit against the same product with 32 zero columns appended to K (the added
 terms are exact zeros, the order over k is the same).  Then K that is no multiple
 of the stages' depth, on every tile, and the loss added up beside the weight
 gradient."""
@@ -10,6 +10,8 @@ import pytest
 import torch
 
 import oracle.uniquan as O
+import test_gpu_decoder_ops as ops
+import test_gpu_fused as fused
 from paper_2506_03781_amd import uniquan as uq
 
 pytestmark = pytest.mark.gpu
@@ -48,10 +50,73 @@ def test_product_layouts_and_stages(M, N, K, a_kslow, b_kslow):
     assert np.all(np.abs(got - ref) <= (K + 1) * 2.0 ** -24 * mag + 1e-30)
 
 
+# K on both sides of the line between the two kernels (512), and above it
+@pytest.mark.parametrize("K", [480, 512, 544, 1088])
+@pytest.mark.parametrize("a_kslow,b_kslow", [(0, 0), (1, 1), (0, 1), (1, 0)])
+def test_product_layouts_deep(K, a_kslow, b_kslow):
+    test_product_layouts_and_stages(4104, 3848, K, a_kslow, b_kslow)
+
+
+# the other epilogues at K from which the four-wavefront kernel takes them and one step below, with full
+# grids of tiles and few, short and whole first stages (the losses and the fused backward: test names of their own)
+@pytest.mark.parametrize("T,H,K,L,group", [(4104, 16, 1248, 4104, 1), (4104, 16, 1312, 513, 4), (520, 4, 32, 260, 1),
+                                           (520, 4, 2528, 260, 2), (520, 4, 2560, 260, 1), (520, 4, 2592, 260, 2)])
+def test_heads_depths(T, H, K, L, group):
+    ops.test_gemm_heads_matches_product_then_split(T, H * 2 if T > 4096 else H, K, L, group, True)
+
+
+@pytest.mark.parametrize("T,I,K", [(4104, 2080, 992), (4104, 2080, 1056), (264, 352, 32), (264, 352, 2016), (264, 352, 2080)])
+def test_swiglu_depths(T, I, K):
+    ops.test_gemm_swiglu_matches_products_then_silu(T, I, K)
+
+
+@pytest.mark.parametrize("T,I,K", [(4104, 4104, 2528), (4104, 4104, 2592), (264, 360, 32), (264, 360, 5088),
+                                   (264, 360, 5152)])
+@pytest.mark.parametrize("stacked", [False, True])
+def test_silu_bwd_depths(T, I, K, stacked):
+    ops.test_gemm_silu_bwd_matches_product_then_silu_bwd(T, I, K, stacked)
+
+
+@pytest.mark.parametrize("K", [480, 544])
+def test_residual_and_block_loss_depths(K):
+    ops.test_gemm_nt_residual(4104, 3848, K)
+    ops.test_gemm_block_loss_matches_product_then_loss(4104, 3848, K)
+
+
+@pytest.mark.parametrize("C", [480, 544, 992, 1056, 1032])
+def test_loss_depths(C):
+    """E and the loss with a target and without, against the product itself: E is its value less the target,
+    rounded to bf16."""
+    T, R = 3848, 4104
+    rs = np.random.default_rng(C)
+    X, Wh = (dev(rs.standard_normal((n, C))) for n in (T, R))
+    Yt = torch.from_numpy(rs.standard_normal((R, T)).astype(F32)).cuda() * 20.0
+    P = torch.empty(R, T, device="cuda")
+    uq.uniquan_gemm_nt(R, T, C, Wh, X, P)
+    ws = torch.empty(uq.uniquan_recon_ws(T, R, C), device="cuda")
+    for target in (Yt, None):
+        Et = torch.full((R, T), float("nan"), device="cuda", dtype=torch.bfloat16)
+        loss = torch.zeros(1, device="cuda")
+        uq.uniquan_layer_recon(T, R, C, X, None, Wh, target, loss, Et, ws, None)
+        e = P - target if target is not None else P
+        torch.cuda.synchronize()
+        assert torch.equal(Et, e.bfloat16())
+        ref = e.double().square().sum().item()
+        assert abs(loss.item() - ref) <= 1e-6 * ref
+
+
+@pytest.mark.parametrize("T,g", [(6112, 128), (6176, 32)])
+def test_fused_backward_depths(T, g):
+    """The straight-through backward in the product's store on both sides of its line (T = 6144 tokens): 17 x 16
+    tiles, ragged in both dimensions."""
+    fused.sampled_rows_check(4100, 3968, T, 3, g, 38, np.array([0, 127, 128, 2049, 4095, 4096, 4099]))
+
+
 @pytest.mark.parametrize("M", [4097, 4351])
-def test_odd_rows(M):
+@pytest.mark.parametrize("K", [128, 576])
+def test_odd_rows(M, K):
     """Rows past M in the last tile are neither read nor written: guard rows stay as they are."""
-    N, K = 4096, 128
+    N = 4096
     rs = np.random.default_rng(M)
     A, B = (O.bf16_rne(rs.standard_normal((n, K)).astype(F32)) for n in (M, N))
     out = torch.full((M + 8, N), 7.0, device="cuda")
