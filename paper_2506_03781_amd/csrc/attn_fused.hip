@@ -37,6 +37,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "uq_launch.h"
 
 namespace uq {
@@ -740,12 +742,39 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(2,
 namespace {
 constexpr int NW = 4, S = 2;  // waves per group of rows, stages
 
+// Longest time that a CU works on split walks, in the units of a row block's
+// number: a CU takes one such workgroup at a time, workgroup w goes to XCD w % 8
+// and there to the first of its 32 CUs that is free, in the order of block_of.
+int64_t split_span(int nblk, int64_t batch) {
+  const bool even = (batch & 7) == 0;  // every XCD has the same list then
+  int64_t span = 0;
+  for (int x = 0; x < (even ? 1 : 8); ++x) {
+    int64_t busy[32] = {};
+    for (int64_t i = 0; 8 * i + x < nblk * batch; ++i) {
+      const int64_t load = nblk - (even ? i : 8 * i + x) % nblk;
+      int64_t& cu = i < 32 ? busy[i] : *std::min_element(busy, busy + 32);
+      cu += load;
+      span = std::max(span, cu);
+    }
+  }
+  return span;
+}
+
 // Whether the walks are split: where workgroups of four waves give about one wave
-// per SIMD, and walks of up to 16 tiles or more repay the exchange.  Forward and
-// backward together, one group against two: 288 workgroups (L = 1056) 141 against
-// 114 us, 256 (L = 2048 / 1024 / 512) 227 / 127 / 76 against 173 / 106 / 70; but
-// 512 (L = 2048 / 1024) 311 / 173 against 313 / 198, 32 (L = 256) 46 against 47.
-bool split_walk(int64_t blocks, int L) { return blocks <= 320 && L >= 512; }
+// per SIMD and walks of up to 16 tiles or more repay the exchange.  Up to one
+// workgroup a CU they do (forward and backward together, one group against two:
+// 128 to 256 workgroups at L = 512 / 1056 / 2048 74-76 / 124-128 / 222-227 us against
+// 68-71 / 102-106 / 170-175).  Above, a second workgroup has to wait for a CU, while two
+// of the unsplit ones share one: that pays as long as what is left over is light
+// and the longest CU's time no more than an eighth above the heaviest block's.  Time
+// split / unsplit by that ratio, 257 to 448 workgroups, L = 512 to 3072: 1.00-1.06
+// 0.77-0.99, 1.09-1.11 0.85-0.95, 1.20-1.22 0.94-1.11, 1.25-1.5 1.12-1.24, 2 1.16-1.23;
+// 512 (L = 2048 / 1024) 1.01 / 1.14.  Short walks: 32 (L = 256) 46 us against 47.
+bool split_walk(int nblk, int64_t batch, int L) {
+  const int64_t blocks = nblk * batch;
+  if (L < 512 || blocks > 448) return false;
+  return blocks <= 256 || 8 * split_span(nblk, batch) <= 9 * nblk;
+}
 
 template <typename Kern>
 void launch(Kern kern, int64_t blocks, int ks, const AttnArgs& a, hipStream_t st) {
@@ -766,9 +795,10 @@ hipError_t launch_attn_fwd(const AttnLaunch& q, hipStream_t st) {
   a.batch = q.batch; a.kv_batch = q.kv_batch; a.L = q.L; a.scale = q.scale;
   a.Q = q.Q; a.K = q.K; a.V = q.V; a.O_out = q.O_out; a.lse = q.lse;
   set_tok(a, q);
-  const int64_t blocks = (q.L + NW * NB - 1) / (NW * NB) * q.batch;
+  const int nblk = (q.L + NW * NB - 1) / (NW * NB);
+  const int64_t blocks = nblk * q.batch;
   const bool tok = q.tok_seqs > 0;
-  if (split_walk(blocks, q.L)) launch(tok ? attn_fwd_kernel<NW, S, true, 2> : attn_fwd_kernel<NW, S, false, 2>, blocks, 2, a, st);
+  if (split_walk(nblk, q.batch, q.L)) launch(tok ? attn_fwd_kernel<NW, S, true, 2> : attn_fwd_kernel<NW, S, false, 2>, blocks, 2, a, st);
   else launch(tok ? attn_fwd_kernel<NW, S, true, 1> : attn_fwd_kernel<NW, S, false, 1>, blocks, 1, a, st);
   return hipGetLastError();
 }
@@ -780,8 +810,9 @@ hipError_t launch_attn_bwd(const AttnLaunch& q, hipStream_t st) {
   a.lse = q.lse; a.delta = q.delta; a.dQ = q.dQ; a.dK = q.dK; a.dV = q.dV;
   set_tok(a, q);
   const bool tok = q.tok_seqs > 0;
-  const int64_t blocks = (q.L + NW * NB - 1) / (NW * NB) * q.batch;
-  const bool split = split_walk(blocks, q.L);
+  const int nblk = (q.L + NW * NB - 1) / (NW * NB);
+  const int64_t blocks = nblk * q.batch;
+  const bool split = split_walk(nblk, q.batch, q.L);
   if (split) launch(tok ? attn_bwd_dq_kernel<NW, S, true, 2> : attn_bwd_dq_kernel<NW, S, false, 2>, blocks, 2, a, st);
   else launch(tok ? attn_bwd_dq_kernel<NW, S, true, 1> : attn_bwd_dq_kernel<NW, S, false, 1>, blocks, 1, a, st);
   hipError_t e = hipGetLastError();

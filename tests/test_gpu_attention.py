@@ -169,10 +169,11 @@ def test_attention_token_major_io(n_seq, H, Hkv, L):
     assert torch.equal(bits(dV_tok), bits(dV_ref)), "dV"
 
 
-# the split walk (at most 320 workgroups of 128 rows, L from 512 on): an odd
+# the split walk (up to 256 workgroups of 128 rows, and up to 448 whose remainder is light, L from 512 on): an odd
 # number of tiles, a last workgroup of one tile, both sides of each bound
 @pytest.mark.parametrize("L,batch,kv_batch,sharp", [(512, 2, 2, 2.0), (544, 3, 1, 3.0), (1056, 2, 1, 1.0),
-                                                    (480, 4, 2, 2.0), (512, 81, 27, 1.0)])
+                                                    (480, 4, 2, 2.0), (512, 81, 27, 1.0), (544, 56, 14, 1.0),
+                                                    (544, 60, 15, 1.0), (640, 51, 17, 2.0), (1536, 37, 37, 1.0)])
 def test_attention_split_walk(L, batch, kv_batch, sharp):
     test_attention_fused(L, batch, kv_batch, sharp)
 
