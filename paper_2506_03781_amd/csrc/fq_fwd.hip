@@ -526,8 +526,8 @@ struct FoldArgs {
   int code_src;
 };
 
-// Each wavefront owns 512 consecutive weights with their groups' tables in its
-// own LDS, as the forward does.  Up to 4 levels the nearest one is found by
+// Each wavefront owns fold_groups consecutive groups, at most 512 weights, with
+// their tables in its own LDS.  Up to 4 levels the nearest one is found by
 // trying all of them from registers (a lane's 8 weights lie in one group), which
 // is the definition of the mapping, first of the smallest |fl(x - q_j)|, in four
 // instructions a level without the dependent LDS reads of a search; from 8 levels
@@ -535,6 +535,19 @@ struct FoldArgs {
 // 11008 x 4096, k = 3, g = 128: 70 us against 106 with workgroup-wide tables, k and
 // the levels as variables and the weights loaded behind the tables (the 7 bytes
 // a weight take 60 us).
+//
+// Groups with many levels for their size are fewer a wavefront, 512 levels (6 KB of
+// LDS) in all: at 1024 and more the tables leave too few wavefronts a CU to hide
+// the ranking's LDS reads (4096 x 4096, g = 8, k = 4: 237 us, k = 7: 51 ms; k = 7 at
+// g = 64: 661 us; with 512 levels 111 us, 3.9 ms and 503 us).
+__host__ __device__ inline int fold_groups(int logg, int k) { return 512 >> (logg > k ? logg : k); }
+
+// LDS of a wavefront: the tables and three words per group.
+__host__ __device__ inline size_t fold_lds_bytes(int logg, int k) {
+  const size_t groups = fold_groups(logg, k);
+  return (((groups << k) * 10 + 15) & ~size_t(15)) + 16 * groups;
+}
+
 template <int WDT, int LOGL>
 __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -542,17 +555,17 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
   constexpr bool scan = LOGL <= 2;
   const TileGeom& g = a.t;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gw = 512 >> g.logg;  // groups per wave
+  const int gw = fold_groups(g.logg, LOGL);
   LevelTables tab;
-  float* s_ds = reinterpret_cast<float*>(carve_tables(tab, smem + size_t(wave) * wave_lds_bytes(g.logg, LOGL, false),
-                                                      gw << LOGL));
+  float* s_ds =
+      reinterpret_cast<float*>(carve_tables(tab, smem + size_t(wave) * fold_lds_bytes(g.logg, LOGL), gw << LOGL));
   float* s_zu = s_ds + gw;
   uint32_t* s_codes = reinterpret_cast<uint32_t*>(s_zu + gw);  // the sorted levels' codes, 4 bits each (scan)
-  const int64_t wbase = (int64_t(blockIdx.x) * (blockDim.x >> 6) + wave) * 512;  // first weight of this wave
-  if (wbase >= g.N) return;                                                      // whole wave past the end
-  const int gv = int(min<int64_t>(512, g.N - wbase)) >> g.logg;                  // valid groups
+  const int64_t gid0 = (int64_t(blockIdx.x) * (blockDim.x >> 6) + wave) * gw;  // first group of this wave
+  const int64_t wbase = gid0 << g.logg;                                        // and its first weight
+  if (wbase >= g.N) return;                                                    // whole wave past the end
+  const int gv = int(min<int64_t>(gw, (g.N - wbase) >> g.logg));               // valid groups
   const int ev = gv << LOGL;
-  const int64_t gid0 = wbase >> g.logg;
 
   // The parameters of the first 64 groups and levels are loaded first and the
   // weights right behind them, so that the tables are built while the weights
@@ -1398,16 +1411,10 @@ hipError_t launch_fq_step(const FqStepLaunch& p, hipStream_t st) {
 template <int WD, int LOGL>
 static hipError_t launch_fold_l(const FoldArgs& a, hipStream_t st) {
   auto kern = fold_kernel<WD, LOGL>;
-  const size_t wave_bytes = wave_lds_bytes(a.t.logg, LOGL, false);
-  const int wpb = fwd_waves_per_block(wave_bytes);
-  const size_t lds = size_t(wpb) * wave_bytes;
-  if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (e != hipSuccess) return e;
-  }
-  const int64_t waves = (a.t.N + 511) / 512;
-  hipLaunchKernelGGL(kern, dim3(unsigned((waves + wpb - 1) / wpb)), dim3(64 * wpb), lds, st, a);
+  constexpr int wpb = kThreads / 64;
+  const int64_t gw = fold_groups(a.t.logg, LOGL), waves = ((a.t.N >> a.t.logg) + gw - 1) / gw;
+  hipLaunchKernelGGL(kern, dim3(unsigned((waves + wpb - 1) / wpb)), dim3(kThreads),
+                     wpb * fold_lds_bytes(a.t.logg, LOGL), st, a);
   return hipGetLastError();
 }
 

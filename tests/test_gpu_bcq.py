@@ -192,11 +192,12 @@ def test_rejects_bad_shapes():
     assert e.value.status == uq.UQ_EUNSUPPORTED
 
 
-# the fold's table forms: 64 groups a wavefront, levels by the scan (k <= 2) and
+# the fold's table forms: 64 groups a wavefront and the 4 that many levels leave, levels by the scan (k <= 2) and
 # by the search, a ragged last wavefront; equal levels and weights half-way
 # between levels (the lower level, the smaller code), zero scales of a level
 @pytest.mark.parametrize("R,C,k,g", [(3, 264, 3, 8), (5, 264, 7, 8), (2, 1040, 4, 16), (7, 640, 2, 128),
-                                     (1, 512, 1, 512), (9, 384, 3, 64), (4, 264, 2, 8)])
+                                     (1, 512, 1, 512), (9, 384, 3, 64), (4, 264, 2, 8),
+                                     (7, 328, 5, 8), (3, 272, 6, 16), (5, 448, 7, 64)])
 @pytest.mark.parametrize("code_src", [0, 1])
 def test_fold_edges(R, C, k, g, code_src):
     rs = np.random.default_rng(R + C + k)
