@@ -526,6 +526,21 @@ struct FoldArgs {
   int code_src;
 };
 
+// Parameters only: a thread per group (131072 groups, k = 3: 2.5 us; as a wavefront
+// per 512 weights, 4 of whose lanes had a group, 6.3).
+template <int K>
+__global__ __launch_bounds__(kThreads) void fold_params_kernel(FoldArgs a) {
+  const int64_t gid = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+  if (gid >= a.t.N >> a.t.logg) return;
+  const float dl = a.delta ? a.delta[gid] : 1.0f, zu = a.z_u ? a.z_u[gid] : 0.0f, zb = a.z_b[gid];
+  float al[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) al[i] = a.alpha[gid * K + i];
+#pragma unroll
+  for (int i = 0; i < K; ++i) a.alpha_star[gid * K + i] = dl * al[i];
+  a.z_star[gid] = dl * (zb - zu);
+}
+
 // Each wavefront owns fold_groups consecutive groups, at most 512 weights, with
 // their tables in its own LDS.  Up to 4 levels the nearest one is found by
 // trying all of them from registers (a lane's 8 weights lie in one group), which
@@ -588,10 +603,8 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
   const int64_t off = wbase + min(lane * kVec, (gv << g.logg) - kVec);
   Raw8<WDT> w;
   float sv[8];
-  if (a.codes != nullptr) {
-    w.load(a.W, off);
-    if (a.code_src == 0) load8f(a.s, off, sv);
-  }
+  w.load(a.W, off);
+  if (a.code_src == 0) load8f(a.s, off, sv);
   auto put_group = [&](int gl, const Group& p) {
     const int64_t gid = gid0 + gl;
 #pragma unroll
@@ -607,13 +620,10 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
     if (a.code_src != 0) zb = p.dl * (zb - p.zu);
     tab.raw[e] = level_value_k<LOGL>(al, zb, e & (L - 1));
   };
-  if (a.codes != nullptr) {
-    if (lane < ev) put_level(lane, pe);
-    for (int e = lane + 64; e < ev; e += 64) put_level(e, load_group(gid0 + (e >> LOGL), false));
-  }
+  if (lane < ev) put_level(lane, pe);
+  for (int e = lane + 64; e < ev; e += 64) put_level(e, load_group(gid0 + (e >> LOGL), false));
   // past every read of the wavefront's parameters, which the results may overwrite
   if (lane < gv) put_group(lane, pg);
-  if (a.codes == nullptr) return;  // uniform across the grid
   wave_lds_sync();
   for (int e = lane; e < ev; e += 64) {
     const int b = e & (L - 1), base = e - b;
@@ -1410,6 +1420,12 @@ hipError_t launch_fq_step(const FqStepLaunch& p, hipStream_t st) {
 
 template <int WD, int LOGL>
 static hipError_t launch_fold_l(const FoldArgs& a, hipStream_t st) {
+  if (a.codes == nullptr) {
+    const int64_t n = a.t.N >> a.t.logg;
+    hipLaunchKernelGGL((fold_params_kernel<LOGL>), dim3(unsigned((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                       a);
+    return hipGetLastError();
+  }
   auto kern = fold_kernel<WD, LOGL>;
   constexpr int wpb = kThreads / 64;
   const int64_t gw = fold_groups(a.t.logg, LOGL), waves = ((a.t.N >> a.t.logg) + gw - 1) / gw;

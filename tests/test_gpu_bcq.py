@@ -242,6 +242,26 @@ def test_fold_in_place(R, C, k, g):
     assert np.array_equal(z.cpu().numpy(), fo["z_star"].reshape(-1))
 
 
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("g", [8, 128])
+def test_fold_params_many_groups(k, g):
+    """No codes: a workgroup's groups and a part of one more, with and without Delta and z_U."""
+    R, C = 299, g
+    rs = np.random.default_rng(k)
+    alpha = rs.uniform(0.1, 2.0, (R, k)).astype(F32)
+    delta, z_u, z_b = (rs.standard_normal(R).astype(F32) for _ in range(3))
+    for d, zu in ((delta, z_u), (None, None)):
+        a, z = torch.empty(R * k, device=DEV), torch.empty(R, device=DEV)
+        uq.uniquan_fold_to_bcq(R, C, k, g, None, None, None, None if d is None else dev(d, torch.float32),
+                               None if zu is None else dev(zu, torch.float32), dev(alpha.reshape(-1), torch.float32),
+                               dev(z_b, torch.float32), a, z)
+        torch.cuda.synchronize()
+        ones, zero = np.ones(R, F32), np.zeros(R, F32)
+        a_ref, z_ref = U.fold_params_f32(alpha, z_b, k, ones if d is None else d, zero if zu is None else zu)
+        assert np.array_equal(a.cpu().numpy().reshape(R, k), a_ref) and np.array_equal(z.cpu().numpy(), z_ref)
+
+
 def expected_terms(X, codes, a, z, g):
     """Y as the product is defined in the header, column by column in fp64: z* - sum_i alpha*_i for every column
     and 2 alpha*_i where bit i is set, the columns whose bit is clear left out of the second."""
