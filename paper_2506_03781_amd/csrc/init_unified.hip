@@ -423,10 +423,17 @@ __device__ __forceinline__ void map_words(const StepTable& t, bool ok, const X& 
   }
 }
 
-__host__ __device__ inline size_t init_wave_lds_bytes(int logg, int k) {
-  const size_t e = (size_t(512) >> logg) << k;  // levels per wave
-  return e * 12 + 16;  // tables of L + 1 levels and words (L >= 2), or raw and sorted levels and codes
+// Mapping by thresholds for groups with a lane per level.
+__host__ __device__ constexpr bool init_step(int logg, int k) { return logg - 3 >= k; }
+
+// A wavefront's tables: of L + 1 levels and words a group, or raw and sorted
+// levels and codes.  The second set the number of workgroups a CU holds for small
+// groups (k = 4, g = 8: 37 KB each, four of them).
+__host__ __device__ constexpr size_t init_wave_lds_bytes(int logg, int k) {
+  const size_t groups = size_t(512) >> logg, e = groups << k;
+  return init_step(logg, k) ? (8 * (e + groups) + 15) & ~size_t(15) : (e * 9 + 15) & ~size_t(15);
 }
+static_assert(4 * init_wave_lds_bytes(3, 4) <= 36 * 1024, "four workgroups a CU at k = 4, g = 8");
 
 template <int WDT, int K, int LOGG>
 __global__ __launch_bounds__(kThreads) void init_unified_kernel(InitArgs a) {
@@ -434,12 +441,14 @@ __global__ __launch_bounds__(kThreads) void init_unified_kernel(InitArgs a) {
   __shared__ uint32_t wordc[1 << K];
   constexpr int L = 1 << K;
   constexpr int lpg = 1 << (LOGG - 3);  // lanes per group
-  constexpr bool kStep = lpg >= L;      // a lane per level: mapping by thresholds
+  constexpr bool kStep = init_step(LOGG, K);
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int jl = lane & (lpg - 1);
-  if (threadIdx.x < L) wordc[threadIdx.x] = code_word<K>(threadIdx.x);
-  __syncthreads();
+  if constexpr (kStep) {
+    if (threadIdx.x < L) wordc[threadIdx.x] = code_word<K>(threadIdx.x);
+    __syncthreads();
+  }
   const int64_t wave_off = (int64_t(blockIdx.x) * (kThreads / 64) + wave) * 512;
   if (wave_off >= a.N) return;  // whole wavefront past the end (no block barriers below)
   const int64_t off = wave_off + lane * 8;
