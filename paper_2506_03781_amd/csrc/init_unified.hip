@@ -423,8 +423,9 @@ __device__ __forceinline__ void map_words(const StepTable& t, bool ok, const X& 
   }
 }
 
-// Mapping by thresholds for groups with a lane per level.
-__host__ __device__ constexpr bool init_step(int logg, int k) { return logg - 3 >= k; }
+// Mapping by thresholds for groups with a lane per level; two levels (k = 1) are found
+// as fast without (2048 x 4096, g = 128, one grid point: 65 us with it, 59 without; 30: equal).
+__host__ __device__ constexpr bool init_step(int logg, int k) { return k > 1 && logg - 3 >= k; }
 
 // A wavefront's tables: of L + 1 levels and words a group, or raw and sorted
 // levels and codes.  The second set the number of workgroups a CU holds for small
