@@ -43,8 +43,9 @@ __device__ __forceinline__ uint32_t gather_bit(uint32_t v, int i) {
 // Blocks from nb2 on: one thread per (quad q, row r, word m), 32 code bytes ->
 // one word per plane.  The others: alpha*, z*_B -> binary16, tiles of 64 rows x 16
 // group columns turned in LDS so that reads run along a row's groups and writes
-// along the rows (11008 x 4096, k = 3, g = 128: 13 us as a kernel of its own
-// with a thread per parameter, whose reads were a row apart, after 12 for the planes; 17 together here).
+// along the rows (11008 x 4096, k = 3, g = 128: 13 us as a kernel of its own with a
+// thread per parameter, whose reads were a row apart, after 12 for the planes; 13
+// together here).
 __global__ __launch_bounds__(256) void bcq_pack_kernel(const uint8_t* __restrict__ codes,
                                                        uint32_t* __restrict__ planes,
                                                        const float* __restrict__ alpha_star,
@@ -58,22 +59,43 @@ __global__ __launch_bounds__(256) void bcq_pack_kernel(const uint8_t* __restrict
     const int64_t r0 = int64_t(rt) * TR, j0 = int64_t(blockIdx.x - rt * nj) * TJ;
     const int nr = int(min<int64_t>(TR, R - r0)), ng = int(min<int64_t>(TJ, gpr - j0));
     auto half = [](float v) { return __builtin_bit_cast(uint16_t, _Float16(v)); };
-    const uint32_t per = ng * k;
-    for (uint32_t e = threadIdx.x; e < nr * per; e += 256) {
-      const uint32_t r = e / per, c = e - r * per, j = c / uint32_t(k);
-      t[c - j * k][j][r] = half(alpha_star[((r0 + r) * gpr + j0) * k + c]);
-    }
-    for (int e = threadIdx.x; e < nr * ng; e += 256) {
-      const int r = e / ng, j = e - r * ng;
-      t[k][j][r] = half(z_star[(r0 + r) * gpr + j0 + j]);
-    }
+    // A lane per column (group, parameter) of 256 >> sh rows, U rows' loads in
+    // flight, no division in the loops: these few workgroups are the launch's end
+    // in a layer of 4096 x 4096 (an element a turn with two divisions: k = 4, g = 256
+    // 9.2 us, the two launches before it 7.9, now 5.8).
+    constexpr int U = 4;
+    const float* ap = alpha_star + (r0 * gpr + j0) * k;  // 32-bit offsets from uniform bases: the tile's
+    const float* zp = z_star + r0 * gpr + j0;            // rows span at most 2^23 elements
+    const int rl = int(gpr) * k;
+    const int per = ng * k, sh = per <= 16 ? 4 : per <= 32 ? 5 : 6, step = 256 >> sh;
+    const int c = threadIdx.x & ((1 << sh) - 1);
+    const int ca = k == 1 ? c : k == 2 ? c >> 1 : k == 3 ? (c * 43) >> 7 : c >> 2;  // c / k (c < 64)
+    const int jz = threadIdx.x & (TJ - 1), rz = threadIdx.x / TJ;
+    float z[TR * TJ / 256];
+#pragma unroll
+    for (int u = 0; u < TR * TJ / 256; ++u)
+      z[u] = zp[min(rz + u * (256 / TJ), nr - 1) * int(gpr) + min(jz, ng - 1)];
+    if (c < per)
+      for (int r = threadIdx.x >> sh; r < nr; r += U * step) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = ap[min(r + u * step, nr - 1) * rl + c];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (r + u * step < nr) t[c - ca * k][ca][r + u * step] = half(v[u]);
+      }
+    if (jz < ng)
+#pragma unroll
+      for (int u = 0; u < TR * TJ / 256; ++u)
+        if (rz + u * (256 / TJ) < nr) t[k][jz][rz + u * (256 / TJ)] = half(z[u]);
     __syncthreads();
-    for (int e = threadIdx.x; e < (k + 1) * ng * TR; e += 256) {
-      const int r = e & (TR - 1), c = e / TR, i = c / ng, j = c - i * ng;
-      if (r >= nr) continue;
-      uint16_t* out = i < k ? alpha16 + int64_t(i) * gpr * R : z16;
-      out[(j0 + j) * R + r0 + r] = t[i][j][r];
-    }
+    const int r = threadIdx.x & (TR - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / TR);
+    const bool few = ng < 256 / TR;  // the wavefronts share the arrays, else the groups
+    if (r < nr)
+      for (int i = few ? w : 0; i <= k; i += few ? 256 / TR : 1) {
+        uint16_t* out = (i < k ? alpha16 + int64_t(i) * gpr * R : z16) + j0 * R + r0;
+        for (int j = few ? 0 : w; j < ng; j += few ? 1 : 256 / TR) out[j * R + r] = t[i][j][r];
+      }
     return;
   }
   const int64_t nq = C / 128;

@@ -78,7 +78,8 @@ def close(y, ref, what=""):
 
 
 @pytest.mark.parametrize("R,C,k,g", [(4, 256, 1, 128), (37, 384, 3, 128), (300, 1024, 4, 256), (5, 640, 2, 640),
-                                     (1024, 2048, 4, 128)])
+                                     (1024, 2048, 4, 128), (65, 2176, 2, 128), (129, 2432, 3, 128), (70, 4224, 4, 128),
+                                     (63, 4352, 1, 128), (200, 1152, 2, 384)])
 def test_pack_bit_exact(R, C, k, g):
     codes, a, z, _ = inputs(1, R, C, k, g, R + C + k)
     codes = codes | (np.random.default_rng(1).integers(0, 2, (R, C)) << 7).astype(np.uint8)  # mask bits ignored
