@@ -355,13 +355,16 @@ constexpr float kUnit = 0x1p-15f;
 template <int K>
 __device__ __forceinline__ float bcq_plain_sum(const BcqArgs& a, int tok, int64_t r, int64_t q, int64_t q_end) {
   float y = 0.0f;
+#pragma unroll 1
   for (; q < q_end; ++q) {
     const int64_t j = q / a.qpg;
     float S = 0.0f, P[K] = {}, asum = 0.0f;
+#pragma unroll 1
     for (int m = 0; m < 4; ++m) {
       uint32_t w[K];
 #pragma unroll
       for (int i = 0; i < K; ++i) w[i] = a.planes[((i * a.nq + q) * a.R + r) * 4 + m];
+#pragma unroll 1
       for (int c = 0; c < 32; ++c) {
         const float x = bf16_to_f32(a.X[tok * a.C + q * 128 + 32 * m + c]);
         S += x;
@@ -528,8 +531,10 @@ __global__ __launch_bounds__(64 * W) void bcq_mfma_kernel(BcqArgs a, int T) {
       for (int r = 0; r < 4; ++r) red[wave][4 * kg + r][16 * t + n] = (1.0f / kUnit) * y[t][r];
   }
   __syncthreads();
-  const int tok = threadIdx.x / ROWS, rr = threadIdx.x % ROWS;
-  if (tok < T && r0 + rr < R) {
+  const int rr = threadIdx.x % ROWS;
+#pragma unroll
+  for (int tok = threadIdx.x / ROWS; tok < 8; tok += 64 * W / ROWS) {
+    if (tok >= T || r0 + rr >= R) break;
     float s = 0.0f;
 #pragma unroll
     for (int w = 0; w < W; ++w) s += red[w][tok][rr];
@@ -596,8 +601,50 @@ static void launch_mm_t(const BcqArgs& a, int T, dim3 grid, hipStream_t st) {
 template <int K>
 static void launch_mfma(const BcqArgs& a, int T, int rt, int w, dim3 grid, hipStream_t st) {
   if (rt == 1) hipLaunchKernelGGL((bcq_mfma_kernel<K, 1, 8>), grid, dim3(512), 0, st, a, T);
+  else if (w == 1) hipLaunchKernelGGL((bcq_mfma_kernel<K, 2, 1>), grid, dim3(64), 0, st, a, T);
   else if (w == 8) hipLaunchKernelGGL((bcq_mfma_kernel<K, 2, 8>), grid, dim3(512), 0, st, a, T);
   else hipLaunchKernelGGL((bcq_mfma_kernel<K, 2, 16>), grid, dim3(1024), 0, st, a, T);
+}
+
+// Whether the table form takes the product; slabs and q: the MFMA form's column
+// slabs and its quads a wavefront.  Never from four rows on, where the MFMA form's
+// time does not grow with the batch.  Below:
+//   above 21 M weights, where the tables read the bits at 4 TB/s (28672 x 8192, k = 3,
+//   one row: 23.5 us against 36; 2000 x 12288, k = 4: 10.1 against 12.0);
+//   one quad and many rows, where the tables need no second launch either (one row,
+//   k = 3: 40000 x 128 3.6 us against 4.0, 28672 3.6 against 3.4; three rows: 65536 5.0 against
+//   4.2, 128256 5.7 against 5.6);
+//   one row of wide layers with three and four planes (28672 x 640, k = 3 6.6 us against
+//   6.9, 24000 6.3 against 6.3);
+//   rows whose chain of quads, at 0.5 to 1 us a quad, is longer than the tables' two
+//   launches (one row, k = 4: 2048 x 7168 7.3 us against 9.2, 5120 7.2 against 7.4; two
+//   rows 8.6 against 9.3, 6144 8.3 against 8.2), or that the MFMA form gives a second
+//   launch of its own for two slabs (2048 x 8192, one row, k = 3: 7.2 against 8.2).
+// Elsewhere the MFMA form's single launch counts (4096 x 4096, one row, k = 3: 6.3 us
+// against 5.7; 512 x 28672: 12.9 against 9.7).
+static bool table_takes(const BcqMatmulLaunch& p, int64_t nq, int64_t slabs, int q) {
+  if (p.T > 3) return false;
+  if (p.R * p.C > (int64_t(5) << 22)) return true;
+  if (nq == 1) return p.R > 32768 * p.T;
+  if (p.R >= 8192) return p.T == 1 && nq > 2 && p.k >= 3 && p.R >= (p.k == 4 && nq > 4 ? 20000 : 28672);
+  return (slabs > 1 && p.T == 1 && p.k > 1 && nq < 96) || ((slabs == 1 || p.T == 1) && q + p.k >= 9 + p.T);
+}
+
+// Slabs for between one and two 32-row workgroups a CU: the CUs with two are twice as
+// long as the others; S slabs cut that to ceil(rb S / 256) / S of a row block's time
+// (0.04 k us a quad) for a second launch and its sums (3 + S us).  9000 x 28672, 4 rows,
+// k = 4: 51 us against 79 (58 in the form before); 12000 x 16384 37 against 48.
+static int64_t fill_slabs(int64_t rb, int64_t nq, int k) {
+  int64_t best = 1;
+  double t = 2.0 * 0.04 * double(k * nq);
+  for (int64_t s = 2; s <= 4; ++s) {
+    const double u = double((rb * s + 255) / 256) / double(s) * 0.04 * double(k * nq) + 3.0 + double(s);
+    if (u < t) {
+      t = u;
+      best = s;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_bcq_matmul(const BcqMatmulLaunch& p, hipStream_t st) {
@@ -613,27 +660,31 @@ hipError_t launch_bcq_matmul(const BcqMatmulLaunch& p, hipStream_t st) {
   a.gpr = p.C / p.g;
   a.qpg = p.g / 128;
   a.qpg_inv = a.qpg > 1 ? uint32_t(((uint64_t(1) << 32) + a.qpg - 1) / a.qpg) : 0;
-  // Tables for one to three batch rows of layers above 21 M weights, where
-  // the bits are read at 4 TB/s (28672 x 8192, k = 3, one row: 23.5 us against
-  // 36 on MFMA; 2000 x 12288, k = 4: 10.1 against 12.0).  Below, the single launch
-  // counts (4096 x 4096, k = 4: 7.2 us against 9.6; 1000 x 4096: 7.1 against 9.6;
-  // 512 x 28672, two launches either way: 9.7 against 12.9), and from four rows
-  // on the MFMA form's time does not grow with the batch.
-  int64_t slabs;
-  if (p.T >= 4 || p.R * p.C <= (int64_t(5) << 22)) {
-    // 16 rows a workgroup where that gives more workgroups than 32 would leave
-    // CUs busy; 16 wavefronts where 32-row workgroups are few and rows long
-    // (8192 x 28672: 36 us against 38; 11008 x 4096: 12.1 against 10.9)
-    const int rt = p.R >= 8192 ? 2 : 1;
-    const int w = rt == 2 && p.R < 16384 && a.nq >= 128 ? 16 : 8;
-    const int64_t rb = (p.R + 16 * rt - 1) / (16 * rt);
-    // slabs only where the rows alone leave CUs idle and a wavefront would still
-    // have four quads (512 x 28672: 9.7 us with 7 slabs, 23 with one)
-    slabs = (256 + rb - 1) / rb;
-    if (slabs > a.nq / (4 * w)) slabs = a.nq / (4 * w);
-    if (slabs < 1) slabs = 1;
-    a.qps = int((a.nq + slabs - 1) / slabs);
-    slabs = (a.nq + a.qps - 1) / a.qps;
+  // The MFMA form: 16 rows a workgroup where that gives more workgroups than 32
+  // would leave CUs busy; eight wavefronts over a row's quads, 16 where one
+  // 32-row workgroup a CU and long rows leave eight alone (8192 x 28672, k = 3: 34 us
+  // against 37; 9000 x 28672, more workgroups than CUs, 64 against 60), one where
+  // there are one or two quads (128256 x 256, 4 rows, k = 3: 7.9 us against 16.5 with
+  // idle ones).
+  const int rt = p.R >= 8192 ? 2 : 1;
+  const int64_t rb = (p.R + 16 * rt - 1) / (16 * rt);
+  const int w = rt == 1 ? 8 : a.nq <= 2 && rb > 512 ? 1 : a.nq >= 128 && rb <= 256 ? 16 : 8;
+  // Column slabs where the rows alone leave CUs idle and a wavefront would still
+  // have four quads (512 x 28672: 9.7 us with 7 slabs, 23 with one): as many as fill
+  // the CUs once, or three where that is one and three nearly fill them twice (4
+  // rows, k = 3: 1536 x 28672 15.7 us against 17.0 with a slab more, 2560 x 16384 12.1
+  // with three against 15.2 with two).
+  int64_t slabs = rb <= 128   ? 256 / rb
+                  : rb <= 170 ? (a.nq >= 96 ? 3 : 1)
+                  : rb < 256  ? (a.nq >= 192 ? 2 : 1)
+                  : rb > 256 && rb < 512 ? fill_slabs(rb, a.nq, p.k)
+                              : 1;
+  if (slabs > a.nq / (4 * w)) slabs = a.nq / (4 * w);
+  if (slabs < 1) slabs = 1;
+  const int64_t qps = (a.nq + slabs - 1) / slabs;
+  slabs = (a.nq + qps - 1) / qps;
+  if (!table_takes(p, a.nq, slabs, int((qps + w - 1) / w))) {
+    a.qps = int(qps);
     a.out = slabs == 1 ? p.Y : p.partials;
     // a launch takes fewer than 2^32 threads
     constexpr int64_t kMaxBlocks = int64_t(1) << 21;

@@ -130,21 +130,25 @@ def test_matmul_partial_last_slab(T):
     sampled(T, 8192, 4224, 3, 128, 25, 48)
 
 
-# the table form (1 to 3 batch rows of layers above 21 M weights): 1, 2 and 4
-# quads a slab, the last slab of 33 quads short, groups of 2, 3, 11 and 16 quads
+# the table form (1 to 3 batch rows of layers above 21 M weights and of some shapes
+# below, the last five): 1, 2 and 4 quads a slab, the last slab of 33 quads short, groups of 2, 3, 11 and 16 quads
 # and of a whole row, last row blocks of one row and of 137
 @pytest.mark.parametrize("T,R,C,k,g", [(1, 5001, 4224, 1, 384), (2, 5001, 4224, 2, 4224), (3, 5001, 4224, 4, 128),
                                        (2, 8193, 4224, 4, 1408), (1, 8193, 4224, 2, 128), (3, 8193, 4224, 1, 384),
-                                       (1, 8193, 8192, 4, 8192), (2, 8193, 8192, 1, 256), (3, 8193, 8192, 2, 2048)])
+                                       (1, 8193, 8192, 4, 8192), (2, 8193, 8192, 1, 256), (3, 8193, 8192, 2, 2048),
+                                       (1, 32769, 128, 2, 128), (1, 2049, 7168, 4, 1024), (1, 515, 8192, 2, 128),
+                                       (2, 300, 7168, 4, 128), (1, 28673, 640, 3, 640)])
 def test_matmul_table_form(T, R, C, k, g):
     sampled(T, R, C, k, g, 33, 48, last=True)
 
 
 # the MFMA form's dispatch: 16-row and 32-row workgroups with a ragged last one,
 # wavefronts with no quad, groups of 3 quads (divided by multiplication), column
-# slabs with partial sums, 16 wavefronts over long rows
+# slabs with partial sums, 16 wavefronts over long rows, one over one or two quads
 @pytest.mark.parametrize("T,R,C,k,g", [(1, 17, 128, 2, 128), (8, 15, 1152, 3, 384), (2, 33, 4224, 1, 1408),
-                                       (3, 40, 16512, 4, 384), (8, 8193, 2048, 2, 2048), (5, 8223, 16384, 1, 128)])
+                                       (3, 40, 16512, 4, 384), (8, 8193, 2048, 2, 2048), (5, 8223, 16384, 1, 128),
+                                       (8, 8191, 16384, 3, 128), (8, 8192, 16384, 2, 256), (8, 8200, 256, 4, 256),
+                                       (1, 20000, 128, 3, 128), (4, 2561, 12416, 2, 128), (6, 4000, 24704, 1, 128)])
 def test_matmul_mfma_dispatch(T, R, C, k, g):
     sampled(T, R, C, k, g, 31, min(R, 48))
 
