@@ -16,15 +16,15 @@
 //
 // Kernels (all bf16 MFMA with fp32 accumulation, v_mfma_f32_32x32x16_bf16
 // unless stated; the same sums in the same order either way):
-//   gemm_w4_kernel    the main one, on 256 x 256 tiles: four wavefronts of 128 x
-//                     128 (v_mfma_f32_16x16x32_bf16), two 64-deep stages, the
+//   gemm_w4_kernel    the main one, on 256 x 256 tiles with K deep enough
+//                     (w4_depth): four wavefronts of 128 x 128
+//                     (v_mfma_f32_16x16x32_bf16), two 64-deep stages, the
 //                     instruction order fixed by hand;
-//   gemm_pp_kernel    256 x 128 tiles, and 256 x 256 tiles of causal or K-slow
-//                     products that the first does not take: eight wavefronts
-//                     in two groups that alternate ("ping-pong") between an
-//                     MFMA phase and a memory phase (LDS fragment reads,
-//                     global_load_lds copies into a ring of 32- or 64-deep
-//                     stages, exact vmcnt waits, barriers);
+//   gemm_pp_kernel    256 x 128 tiles, and 256 x 256 tiles with a shallower K:
+//                     eight wavefronts in two groups that alternate
+//                     ("ping-pong") between an MFMA phase and a memory phase
+//                     (LDS fragment reads, global_load_lds copies into a ring
+//                     of 32- or 64-deep stages, exact vmcnt waits, barriers);
 //   gemm_pipe_kernel  four wavefronts, the same direct-to-LDS stage ring, for
 //                     128 x 128 tiles (shapes too small to fill the GPU with
 //                     256-row tiles);
@@ -540,9 +540,11 @@ __device__ __forceinline__ void reduce_loss(const float* __restrict__ partials, 
 }
 
 // The workgroup past the tiles of a weight-gradient product adds up the loss
-// partials of the product before it: it runs beside the last tiles, where a
-// launch of its own took 5 us of the stream (layer step 4096 x 4096: 178 us).
-// True in that workgroup, which is then done.
+// partials of the product before it, for a launch less (5 us of the stream, of
+// which a 256 x 256 layer's step gains 1.5-2).  It runs beside the tiles where they
+// leave a CU idle; where they fill every CU once (256 tiles of 128 KB of LDS, the
+// 4096 x 4096 layer) it starts when the first tile has ended, and the step's time
+// stays as it was with the launch.  True in that workgroup, which is then done.
 template <int EPI>
 __device__ __forceinline__ bool extra_workgroup(const GemmArgs& p, void* smem) {
   if constexpr (EPI == EPI_GRAD_BF16 || EPI == EPI_GRAD_F32) {
@@ -881,7 +883,7 @@ __global__ __launch_bounds__(256) void gemm_pipe_kernel(GemmArgs p) {
 
 // ---------------------------------------------------------------------------
 // Ping-pong main loop for products on 256 x 128 tiles, and on 256 x 256 tiles
-// where K % 64 == 32.
+// below the K that gemm_w4_kernel takes (K % 32 == 0 there).
 // Eight wavefronts in two groups of four, one wavefront of each group per
 // SIMD.  The groups alternate between an MFMA phase on fragments held in
 // registers and a memory phase (the next stage's fragments from LDS, this
@@ -1118,8 +1120,8 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// Main loop for 256 x 256 tiles with K a multiple of 64: four wavefronts, one
-// per SIMD, each a 128 x 128 tile of v_mfma_f32_16x16x32_bf16 (256
+// Main loop for 256 x 256 tiles with K of 64 and more (a short first stage where
+// it is no multiple of 64): four wavefronts, one per SIMD, each a 128 x 128 tile of v_mfma_f32_16x16x32_bf16 (256
 // accumulator registers), 64-deep stages (128-byte rows) in two LDS buffers.
 //
 // Why this shape.  Per 64-deep stage the four wavefronts read 128 KB of
@@ -1132,8 +1134,8 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(GemmArgs p) {
 //
 // With one wavefront per SIMD every instruction that cannot issue idles the
 // matrix core, so the order is fixed instruction by instruction (n counts the
-// stage's 128 MFMAs; the MFMAs are asm so that the accumulators stay where
-// they are, and scheduling barriers hold the rest between them):
+// stage's 128 MFMAs; all but the last three of a half stage are asm so that the
+// accumulators stay where they are, and scheduling barriers hold the rest between):
 //   n = 0 ..      fragments of the stage's second half, one per two MFMAs;
 //   n = kBar1     they are in registers (and every wavefront's are: barrier),
 //                 so the copies of stage k + 2 into this buffer start, one
@@ -1474,8 +1476,8 @@ static hipError_t launch_bm(const GemmLaunch& q, hipStream_t st) {
 }
 
 // Weight-gradient GEMM with the fused straight-through backward: 256 x 256
-// tiles, on the ping-pong kernel where there are at least 256 of them and on
-// the pipelined kernel otherwise; both use 128-column wave tiles, which hold
+// tiles, by launch_256 where there are at least 256 of them and on the
+// pipelined kernel otherwise; both use 128-column wave tiles, which hold
 // whole groups for g <= 128.  K % 32 == 0.
 hipError_t launch_gemm_ste(const GemmLaunch& q, int k, hipStream_t st) {
   GemmArgs a;
@@ -1484,8 +1486,7 @@ hipError_t launch_gemm_ste(const GemmLaunch& q, int k, hipStream_t st) {
   a.ste = q.ste;
   a.bsa = a.bsb = a.bso = 0;
   a.causal = 0;
-  // four-wavefront or ping-pong kernel (4 x 2 wave grid: 64 x 128 wave tiles)
-  // where the shape gives at least one 256 x 256 tile per CU
+  // (ping-pong kernel: 4 x 2 wave grid, 64 x 128 wave tiles)
   if (tiles<256, 256>(q.M, q.N) >= 256) {
     a.tiles_m = int((q.M + 255) / 256);
     a.tiles_n = int((q.N + 255) / 256);
