@@ -766,14 +766,15 @@ int64_t split_span(int nblk, int64_t batch) {
 // 128 to 256 workgroups at L = 512 / 1056 / 2048 74-76 / 124-128 / 222-227 us against
 // 68-71 / 102-106 / 170-175).  Above, a second workgroup has to wait for a CU, while two
 // of the unsplit ones share one: that pays as long as what is left over is light
-// and the longest CU's time no more than an eighth above the heaviest block's.  Time
-// split / unsplit by that ratio, 257 to 448 workgroups, L = 512 to 3072: 1.00-1.06
-// 0.77-0.99, 1.09-1.11 0.85-0.95, 1.20-1.22 0.94-1.11, 1.25-1.5 1.12-1.24, 2 1.16-1.23;
-// 512 (L = 2048 / 1024) 1.01 / 1.14.  Short walks: 32 (L = 256) 46 us against 47.
+// and the longest CU's time not much above the heaviest block's.  Time split / unsplit
+// by that ratio, L = 512 to 3072: 257 to 320 workgroups 1.00 0.77-0.98, 1.09-1.18
+// 0.91-0.97, 1.20-1.33 0.79-0.98 from seven row blocks on and 0.97-1.24 below, 1.5 and 2
+// 1.12-1.24; up to 448 workgroups 1.00-1.09 0.77-0.85, 1.14 0.96, 1.22-1.33 0.95-1.05; 512
+// (L = 2048 / 1024) 1.01 / 1.14.  Short walks: 32 workgroups (L = 256) 46 us against 47.
 bool split_walk(int nblk, int64_t batch, int L) {
   const int64_t blocks = nblk * batch;
   if (L < 512 || blocks > 448) return false;
-  return blocks <= 256 || 8 * split_span(nblk, batch) <= 9 * nblk;
+  return blocks <= 256 || 24 * split_span(nblk, batch) <= (nblk >= 7 && blocks <= 320 ? 32 : 27) * nblk;
 }
 
 template <typename Kern>
