@@ -563,7 +563,7 @@ __host__ __device__ inline size_t fold_lds_bytes(int logg, int k) {
   return (((groups << k) * 10 + 15) & ~size_t(15)) + 16 * groups;
 }
 
-template <int WDT, int LOGL>
+template <int WDT, int LOGL, int SRC>
 __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr int L = 1 << LOGL, K = LOGL;
@@ -604,7 +604,7 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
   Raw8<WDT> w;
   float sv[8];
   w.load(a.W, off);
-  if (a.code_src == 0) load8f(a.s, off, sv);
+  if (SRC == 0) load8f(a.s, off, sv);
   auto put_group = [&](int gl, const Group& p) {
     const int64_t gid = gid0 + gl;
 #pragma unroll
@@ -616,8 +616,8 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
   auto put_level = [&](int e, const Group& p) {
     float al[K], zb = p.zb;
 #pragma unroll
-    for (int i = 0; i < K; ++i) al[i] = a.code_src == 0 ? p.al[i] : p.dl * p.al[i];  // 1: the folded levels
-    if (a.code_src != 0) zb = p.dl * (zb - p.zu);
+    for (int i = 0; i < K; ++i) al[i] = SRC == 0 ? p.al[i] : p.dl * p.al[i];  // 1: the folded levels
+    if (SRC != 0) zb = p.dl * (zb - p.zu);
     tab.raw[e] = level_value_k<LOGL>(al, zb, e & (L - 1));
   };
   if (lane < ev) put_level(lane, pe);
@@ -661,7 +661,7 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     float x = w.get(i);
-    if (a.code_src == 0) {
+    if (SRC == 0) {
       const float den = ds * sv[i];
       x = x / den + zu;
     }
@@ -1426,7 +1426,7 @@ static hipError_t launch_fold_l(const FoldArgs& a, hipStream_t st) {
                        a);
     return hipGetLastError();
   }
-  auto kern = fold_kernel<WD, LOGL>;
+  auto kern = a.code_src == 0 ? fold_kernel<WD, LOGL, 0> : fold_kernel<WD, LOGL, 1>;
   constexpr int wpb = kThreads / 64;
   const int64_t gw = fold_groups(a.t.logg, LOGL), waves = ((a.t.N >> a.t.logg) + gw - 1) / gw;
   hipLaunchKernelGGL(kern, dim3(unsigned((waves + wpb - 1) / wpb)), dim3(kThreads),
