@@ -712,8 +712,10 @@ uq_status uniquan_bcq_pack(int64_t R, int64_t C, int k, int g,
  * X [T*C] bf16 (8-byte aligned), Y [T*R] fp32 out.  Per group the kernel
  * uses sum_c sigma_i x_c = 2 P_i - S (S: the group's activation sum, P_i:
  * the sum over columns whose bit i is set), P_i from 16-entry subset-sum
- * tables of 4 activations for T <= 3 of large layers and from bf16 MFMA
- * products of the activations with the planes otherwise; fp32 accumulation,
+ * tables of 4 activations for T <= 3 of large layers and of some smaller
+ * shapes (one quad of 128 columns and many rows, long rows with many quads a
+ * wavefront), and from bf16 MFMA products of the activations with the planes
+ * otherwise; fp32 accumulation,
  * deterministic order.  In every form a column whose bit is clear is left out
  * of P_i exactly, so an activation of any size at a weight with every bit clear
  * enters as (z* - sum_i alpha*_i) x only, and an infinite one gives an

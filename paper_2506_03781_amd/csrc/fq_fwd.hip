@@ -546,8 +546,9 @@ __global__ __launch_bounds__(kThreads) void fold_params_kernel(FoldArgs a) {
 // trying all of them from registers (a lane's 8 weights lie in one group), which
 // is the definition of the mapping, first of the smallest |fl(x - q_j)|, in four
 // instructions a level without the dependent LDS reads of a search; from 8 levels
-// on the search is shorter (k = 3: 70 us against 75 for the scan).
-// 11008 x 4096, k = 3, g = 128: 70 us against 106 with workgroup-wide tables, k and
+// on the search is shorter (k = 3: 70 us against 75 for the scan, before the
+// source of the codes was a template argument).
+// 11008 x 4096, k = 3, g = 128: 65 us against 106 with workgroup-wide tables, k and
 // the levels as variables and the weights loaded behind the tables (the 7 bytes
 // a weight take 60 us).
 //

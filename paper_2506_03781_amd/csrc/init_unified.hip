@@ -272,10 +272,10 @@ __device__ __forceinline__ void build_table(float* raw, float* qs, uint8_t* cof,
 }
 
 // ---------------------------------------------------------------------------
-// The round's mapping step for groups with a lane per level.
+// The round's mapping step for groups with a lane per level (k > 1).
 //
-// The kernel is bound by vector issue (100% of the cycles), so the step counts
-// instructions.  Where neighbouring levels are separated by more than 2^-20 of
+// The kernel is bound by vector issue (every cycle at four per instruction, by the
+// counters of 4096 x 4096 at k = 4), so the step counts instructions.  Where neighbouring levels are separated by more than 2^-20 of
 // any distance that can occur, their distances from a weight stay apart after
 // rounding: there is no run of equal distances to walk back, and the nearest
 // level is one of the two around the weight.  A level of -infinity in front
